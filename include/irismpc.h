@@ -60,7 +60,10 @@ typedef int imc_status;
 
 /* Dot-product kernel configurations (imc_params.flags bits 0-3).  All give
  * identical results; they differ in tiling and in how rotations are formed. */
-#define IMC_DOT_TILES_AUTO 0             /* ROTATION when r >= 13, else EXPANDED_256x128 */
+#define IMC_DOT_TILES_AUTO 0             /* pairs of rotations (three products over half of k)
+                                            for 27..31 consecutive rotations when the call has
+                                            enough tiles, else ROTATION when r >= 13, else
+                                            EXPANDED_256x128 */
 #define IMC_DOT_TILES_EXPANDED_256x128 1 /* rotated rows expanded into scratch; 256 x 128 tiles,
                                             8 waves of 64 x 64, global loads 4 K-steps ahead */
 #define IMC_DOT_TILES_EXPANDED_128x128 2 /* as 1 with 128 x 128 tiles, 4 waves */

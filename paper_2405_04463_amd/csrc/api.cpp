@@ -234,6 +234,10 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
   const bool rot_tiles = tiles == IMC_DOT_TILES_AUTO || tiles == IMC_DOT_TILES_ROTATION ||
                          tiles == IMC_DOT_TILES_ROTATION_LDSCOPY || tiles == IMC_DOT_TILES_ROTATION_DIRECT;
   const int kind = tiles == IMC_DOT_TILES_ROTATION_LDSCOPY ? 2 : tiles == IMC_DOT_TILES_ROTATION_DIRECT ? 3 : 0;
+  if (tiles == IMC_DOT_TILES_AUTO && imc::pair_dot_applies(uint32_t(q), uint32_t(ids->r), ids->rot, n, mask_dot != nullptr))
+    return dev_status(imc::launch_pair_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r),
+                                           ids->rot, static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot,
+                                           mask_dot, ld, hipStream_t(stream), galois));
   if (rot_tiles && imc::rot_dot_applies(uint32_t(ids->r), kind)) {
     // rotations read straight from the unrotated operand staged in LDS
     return dev_status(imc::launch_rot_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,

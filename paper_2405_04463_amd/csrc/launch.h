@@ -36,6 +36,10 @@ hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, u
                           const int8_t* b,
                           uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
                           hipStream_t s, int kind, bool galois);
+bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask);
+hipError_t launch_pair_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
+                           const int8_t* b, uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask,
+                           uint64_t ld, hipStream_t s, bool galois);
 // One query group of a fused rotation-aware launch (imc_dot_shares_groups).
 struct DotGroup {
   const int8_t* qop;
