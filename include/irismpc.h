@@ -117,7 +117,8 @@ typedef struct imc_ids {
 
 /* Create a context on HIP device `device`.  Copies the keys, allocates the
  * internal scratch (rotated query operands for params->max_rows rows, about
- * 102,400 B per row, and a few counters) and, the first time on a device,
+ * 102,400 B per row, 32 MiB for the parts of dot products whose K loop is
+ * split, and a few counters) and, the first time on a device,
  * looks up the device address of the static array that
  * imc_dot_shares_rows_noalloc uses.  Errors: IMC_EINVAL (null),
  * IMC_EUNSUPPORTED (code_bits, thr_a, flags; device index >= 64),

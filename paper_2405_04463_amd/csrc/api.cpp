@@ -24,7 +24,14 @@ struct imc_ctx {
   int8_t* rot_op;                 // rotated query operand, max_rows (rounded to 32) rows
   size_t rot_op_bytes;
   unsigned long long* bad;        // open-check counter
+  imc::DotScratch parts;          // parts of a split dot product's K loop
+  bool parts_owned;               // set by the first call that may split ...
+  hipStream_t parts_stream;       // ... on this stream
 };
+
+// 1,984 rows x 64 entries in 16 parts of both vectors take half of it; a call
+// with more outputs has more tiles, and needs fewer parts.
+constexpr size_t kPartBytes = size_t(32) << 20;
 
 // Device array behind imc_dot_shares_rows_noalloc: the expanded rotated query
 // rows of one call (IMC_NOALLOC_MAX_ROWS rows in blocks of 32).  Each GPU the
@@ -84,6 +91,24 @@ imc_status check_ids(const imc_ids* ids) {
   if (ids->first_entry_id % 64) return IMC_EINVAL;
   if (ids->query_id_base >= (1ull << 48)) return IMC_EINVAL;
   return IMC_OK;
+}
+
+// The parts scratch for a call on `stream`.  One stream owns it, the first one
+// that asks: its calls run in order.  Calls on other streams, and captured
+// ones (a graph may be replayed beside eager calls), do not split.
+imc::DotScratch parts_for(imc_ctx* c, hipStream_t stream) {
+  imc::DotScratch none;
+  none.cus = c->parts.cus;
+  if (c->parts_owned && c->parts_stream != stream) return none;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return none;
+  }
+  if (st != hipStreamCaptureStatusNone) return none;
+  c->parts_owned = true;
+  c->parts_stream = stream;
+  return c->parts;
 }
 
 size_t blocks_for(size_t capacity) { return (capacity + 31) / 32; }
@@ -148,10 +173,21 @@ imc_status imc_create(const imc_params* p, int device, imc_ctx** out) {
     delete c;
     return IMC_ENOMEM;
   }
-  const imc_status rs = resolve_scratch(device);   // the device is current (guard above)
+  if (hipMalloc(reinterpret_cast<void**>(&c->parts.part), kPartBytes) != hipSuccess) {
+    (void)hipFree(c->rot_op);
+    (void)hipFree(c->bad);
+    delete c;
+    return IMC_ENOMEM;
+  }
+  c->parts.bytes = kPartBytes;
+  imc_status rs = resolve_scratch(device);   // the device is current (guard above)
+  if (rs == IMC_OK &&
+      hipDeviceGetAttribute(&c->parts.cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+    rs = IMC_EDEVICE;
   if (rs != IMC_OK) {
     (void)hipFree(c->rot_op);
     (void)hipFree(c->bad);
+    (void)hipFree(c->parts.part);
     delete c;
     return rs;
   }
@@ -165,6 +201,7 @@ void imc_destroy(imc_ctx* c) {
   (void)hipDeviceSynchronize();
   (void)hipFree(c->rot_op);
   (void)hipFree(c->bad);
+  (void)hipFree(c->parts.part);
   delete c;
 }
 
@@ -234,7 +271,8 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
   const bool rot_tiles = tiles == IMC_DOT_TILES_AUTO || tiles == IMC_DOT_TILES_ROTATION ||
                          tiles == IMC_DOT_TILES_ROTATION_LDSCOPY || tiles == IMC_DOT_TILES_ROTATION_DIRECT;
   const int kind = tiles == IMC_DOT_TILES_ROTATION_LDSCOPY ? 2 : tiles == IMC_DOT_TILES_ROTATION_DIRECT ? 3 : 0;
-  if (tiles == IMC_DOT_TILES_AUTO && imc::pair_dot_applies(uint32_t(q), uint32_t(ids->r), ids->rot, n, mask_dot != nullptr))
+  if (tiles == IMC_DOT_TILES_AUTO &&
+      imc::pair_dot_applies(uint32_t(q), uint32_t(ids->r), ids->rot, n, mask_dot != nullptr, c->parts.cus))
     return dev_status(imc::launch_pair_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r),
                                            ids->rot, static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot,
                                            mask_dot, ld, hipStream_t(stream), galois));
@@ -242,14 +280,15 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
     // rotations read straight from the unrotated operand staged in LDS
     return dev_status(imc::launch_rot_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
                                           static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot, mask_dot,
-                                          ld, hipStream_t(stream), kind, galois));
+                                          ld, hipStream_t(stream), kind, galois, parts_for(c, hipStream_t(stream))));
   }
   const uint32_t rows_pad = uint32_t(blocks_for(rows) * 32);
   hipError_t e = imc::launch_expand(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
                                     c->rot_op, rows_pad, hipStream_t(stream), galois);
   if (e != hipSuccess) return IMC_EDEVICE;
   e = imc::launch_dot(c->rot_op, uint32_t(rows), rows_pad / 32, static_cast<const int8_t*>(db), ids->first_entry_id,
-                      n, code_dot, mask_dot, ld, hipStream_t(stream), v, galois);
+                      n, code_dot, mask_dot, ld, hipStream_t(stream), v, galois,
+                      parts_for(c, hipStream_t(stream)));
   return dev_status(e);
 }
 
@@ -283,7 +322,8 @@ imc_status dot_shares_rows_impl(imc_ctx* c, int party, const void* qop, size_t q
   if ((v & 0xF) == IMC_DOT_TILES_AUTO || (v & 0xF) >= IMC_DOT_TILES_ROTATION)
     v = (v & ~0xF) | IMC_DOT_TILES_EXPANDED_256x128;
   e = imc::launch_dot(a, uint32_t(nrows), rows_pad / 32, static_cast<const int8_t*>(db), first_entry_id, n,
-                      code_dot, mask_dot, ld, hipStream_t(stream), v, galois);
+                      code_dot, mask_dot, ld, hipStream_t(stream), v, galois,
+                      parts_for(c, hipStream_t(stream)));
   return dev_status(e);
 }
 

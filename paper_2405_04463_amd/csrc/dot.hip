@@ -121,6 +121,8 @@ struct DotArgs {
   uint64_t n;            // columns
   uint32_t mt, nt;       // tiles along rows / columns
   uint32_t persistent;   // grid smaller than the tile count: loop over tiles
+  uint32_t splits, steps_per;   // SPLIT: workgroups per tile, K-steps of each
+  uint32_t* part;        // SPLIT: u32 [vec][split][rows][n]
 };
 
 template <int WM, int WN, int WAVES_M, int WAVES_N>
@@ -134,7 +136,7 @@ struct DotCfg {
   static_assert(kChunksPerStep % kThreads == 0, "chunks must divide evenly");
 };
 
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS>
+template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, bool SPLIT = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs args) {
   using C = DotCfg<WM, WN, WAVES_M, WAVES_N>;
   using G = Geo<K>;
@@ -150,12 +152,15 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
   // tile sequence with stride gridDim.x / 8; otherwise one tile per workgroup.
   const uint32_t i = blockIdx.x;
   const uint32_t xcd = i & 7;
-  const uint32_t s_end = ((args.nt + 7) / 8) * args.mt;
+  // SPLIT: (column tile, part of the K loop) pairs take the place of column tiles.
+  const uint32_t ntp = SPLIT ? args.nt * args.splits : args.nt;
+  const uint32_t s_end = ((ntp + 7) / 8) * args.mt;
   const uint32_t s_step = args.persistent ? (gridDim.x >> 3) : s_end;
   for (uint32_t s = i >> 3; s < s_end; s += s_step) {
   const uint32_t u = s % args.mt, tg = s / args.mt;
-  const uint32_t t = tg * 8 + xcd;
-  if (t >= args.nt) continue;
+  const uint32_t tp = tg * 8 + xcd;
+  if (tp >= ntp) continue;
+  const uint32_t t = SPLIT ? tp / args.splits : tp, part = SPLIT ? tp % args.splits : 0;
 
   // Global source of each 16-byte chunk this thread stages per K-step.
   // Chunk c: block (A row-blocks first, then B entry-blocks), plane, k-chunk, slot.
@@ -188,6 +193,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
 
   constexpr int kSteps = G::kChunks / 2;   // steps of 32 bytes of k
   static_assert(kSteps % NSETS == 0, "the K loop is unrolled by NSETS");
+  const int k_b = SPLIT ? int(part * args.steps_per) : 0;
+  const int k_e = SPLIT ? min(k_b + int(args.steps_per), kSteps) : kSteps;
   v4i rs[NSETS][C::kPerThread];
 #define IMC_GLOAD(R, KS)                                                              \
   _Pragma("unroll") for (int c_ = 0; c_ < C::kPerThread; ++c_)                        \
@@ -220,16 +227,16 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
   v4i nalo[WM], nahi[WM], nblo[WN], nbhi[WN];     // fragments of the next step
   {
     v4i r0[C::kPerThread];
-    IMC_GLOAD(r0, 0)
-    IMC_LSTORE(r0, 0)
-    IMC_GLOAD(r0, 1)
-    IMC_LSTORE(r0, 1)
+    IMC_GLOAD(r0, k_b)
+    IMC_LSTORE(r0, k_b % 3)
+    IMC_GLOAD(r0, k_b + 1)
+    IMC_LSTORE(r0, (k_b + 1) % 3)
   }
 #pragma unroll
-  for (int set = 0; set < NSETS; ++set) { IMC_GLOAD(rs[set], set + 2) }
+  for (int set = 0; set < NSETS; ++set) { IMC_GLOAD(rs[set], min(k_b + set + 2, k_e - 1)) }
   __syncthreads();
-  IMC_FRAGS(falo, fahi, fblo, fbhi, 0)
-  for (int k0 = 0; k0 < kSteps; k0 += NSETS) {
+  IMC_FRAGS(falo, fahi, fblo, fbhi, k_b % 3)
+  for (int k0 = k_b; k0 < k_e; k0 += NSETS) {
 #pragma unroll
     for (int uu = 0; uu < NSETS; ++uu) {
       const int k = k0 + uu;
@@ -244,7 +251,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
         }
       IMC_LSTORE(rs[uu], (k + 2) % 3)             // step k + 2
       __syncthreads();
-      IMC_GLOAD(rs[uu], min(k + 2 + NSETS, kSteps - 1))
+      IMC_GLOAD(rs[uu], min(k + 2 + NSETS, k_e - 1))
 #pragma unroll
       for (int x = 0; x < WM; ++x) { falo[x] = nalo[x]; fahi[x] = nahi[x]; }
 #pragma unroll
@@ -270,7 +277,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
         const uint32_t row = u * C::kBM + (wm * WM + x) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
         if (row < args.rows) {
           const uint32_t z = uint32_t(acc0[x][y][e]) + (uint32_t(acc1[x][y][e]) << 8);
-          out[uint64_t(row) * args.ld + col] = uint16_t(z);
+          if (SPLIT)
+            args.part[((uint64_t(vec) * args.splits + part) * args.rows + row) * args.n + col] = z;
+          else
+            out[uint64_t(row) * args.ld + col] = uint16_t(z);
         }
       }
     }
@@ -293,8 +303,31 @@ hipError_t launch_expand(const int8_t* qop, const uint32_t* qidx, uint32_t q, ui
   return hipGetLastError();
 }
 
+// Adds the parts of a split K loop: u32 [vec][split][rows][n] -> u16 [rows][ld] per vector.
+__global__ void __launch_bounds__(256) reduce_parts_kernel(const uint32_t* __restrict__ part, uint32_t splits,
+                                                           uint64_t count, uint64_t n, uint16_t* code, uint16_t* mask,
+                                                           uint64_t ld) {
+  const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  const uint32_t* p = part + uint64_t(blockIdx.z) * splits * count + i;
+  uint32_t z = 0;
+#pragma unroll 4
+  for (uint32_t k = 0; k < splits; ++k) z += p[k * count];
+  (blockIdx.z ? mask : code)[i / n * ld + i % n] = uint16_t(z);
+}
+
+hipError_t launch_reduce_parts(const uint32_t* part, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
+                               uint16_t* mask, uint64_t ld, hipStream_t s) {
+  const uint64_t count = rows * n;
+  if (!fits_grid(count, 256)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(reduce_parts_kernel, dim3(unsigned((count + 255) / 256), 1, mask ? 2 : 1), dim3(256), 0, s, part,
+                     splits, count, n, code, mask, ld);
+  return hipGetLastError();
+}
+
 template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS>
-static hipError_t launch_dot_cfg(DotArgs d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent) {
+static hipError_t launch_dot_cfg(DotArgs d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
+                                 const DotScratch& scratch, uint32_t per_cu = 1) {
   using C = DotCfg<WM, WN, WAVES_M, WAVES_N>;
   d.mt = (rows + C::kBM - 1) / C::kBM;
   d.nt = uint32_t((n + C::kBN - 1) / C::kBN);
@@ -314,6 +347,30 @@ static hipError_t launch_dot_cfg(DotArgs d, uint32_t rows, uint64_t n, hipStream
   }
   const dim3 grid(blocks, 1, d.out[1] ? 2 : 1);   // z: code, mask (no mask dot when masks are public)
   const size_t lds = 3 * size_t(C::kStageBytes);
+  // Split the K loop while CUs are left over, in pieces of 10 steps: a call of
+  // few tiles takes as long as one workgroup's 800 steps.  1 row x 100
+  // entries 428 -> 18 us, 33 rows x 5,000 entries 448 -> 139.
+  constexpr uint32_t kPieces = Geo<K>::kChunks / 2 / 10;
+  static_assert(10 % NSETS == 0, "a piece is whole unrolled iterations");
+  const uint32_t splits =
+      dot_splits(uint64_t(d.mt) * d.nt * grid.z, per_cu, kPieces, uint64_t(rows) * n * grid.z, scratch);
+  if (splits > 1) {
+    d.steps_per = (kPieces + splits - 1) / splits * 10;
+    d.splits = (kPieces * 10 + d.steps_per - 1) / d.steps_per;
+    d.part = scratch.part;
+    d.persistent = 0;
+    auto kern = dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, true>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    const uint32_t ntp = (d.nt * d.splits + 7) / 8 * 8;
+    hipLaunchKernelGGL(kern, dim3(ntp * d.mt, 1, grid.z), dim3(C::kThreads), lds, s, d);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_reduce_parts(d.part, d.splits, rows, n, d.out[0], d.out[1], d.ld, s);
+  }
+  d.splits = d.steps_per = 0;
+  d.part = nullptr;
   auto kern = dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
@@ -336,18 +393,28 @@ hipError_t launch_expand_rows(const int8_t* qop, uint32_t q, const imc_row* rows
 }
 
 template <int K>
-static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t s, int variant) {
+static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t s, int variant,
+                               const DotScratch& scratch) {
   const bool persistent = (variant & IMC_DOT_PERSISTENT) != 0;
   switch (variant & 0xF) {
-    case 2: return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, persistent);    // 128 x 128, 4 waves of 64 x 64
-    case 3: return launch_dot_cfg<K, 2, 2, 4, 2, 1>(d, rows, n, s, persistent);    // 256 x 128, loads 3 steps ahead
-    default: return launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, rows, n, s, persistent);   // 256 x 128, loads 4 steps ahead
+    case 2: return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, persistent, scratch);    // 128 x 128, 4 waves of 64 x 64
+    case 3: return launch_dot_cfg<K, 2, 2, 4, 2, 1>(d, rows, n, s, persistent, scratch);    // 256 x 128, loads 3 steps ahead
+    default: break;
   }
+  // Few rows: the database stream bounds the call, and a 256-row tile spends
+  // its steps on empty rows with one workgroup a CU waiting for its loads.
+  // Up to 64 rows 64 x 128 tiles (36 KB of LDS, four workgroups a CU), up to
+  // 128 rows 128 x 128 tiles (two).  us against 65,536 entries, 256-row /
+  // these tiles: 1 row 2,158 / 1,125, 64 rows 2,484 / 1,178, 65 rows 2,190 /
+  // 1,551, 128 rows 2,474 / 1,694; 200 rows 2,448 / 2,901 (two row tiles).
+  if (!persistent && rows <= 64) return launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rows, n, s, false, scratch, 4);
+  if (!persistent && rows <= 128) return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, false, scratch, 2);
+  return launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, rows, n, s, persistent, scratch);   // 256 x 128, loads 4 steps ahead
 }
 
 hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const int8_t* b, uint64_t first_entry,
                       uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld, hipStream_t s, int variant,
-                      bool galois) {
+                      bool galois, const DotScratch& scratch) {
   if (rows == 0 || n == 0) return hipSuccess;
   DotArgs d;
   d.a = a;
@@ -360,7 +427,8 @@ hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const i
   d.b_block0 = first_entry / 32;
   d.b_blocks = (n + 31) / 32;
   d.n = n;
-  return galois ? launch_dot_k<kKGalois>(d, rows, n, s, variant) : launch_dot_k<kK>(d, rows, n, s, variant);
+  return galois ? launch_dot_k<kKGalois>(d, rows, n, s, variant, scratch)
+                : launch_dot_k<kK>(d, rows, n, s, variant, scratch);
 }
 
 }  // namespace imc

@@ -31,12 +31,33 @@ hipError_t launch_galois_append(const uint16_t* const raw[3], uint64_t qi, uint8
 
 hipError_t launch_expand(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot, int8_t* a,
                          uint32_t rows_pad, hipStream_t s, bool galois);
+// Scratch of a dot call: where the parts of a split K loop go (u32 sums), and
+// the CUs of the device.
+struct DotScratch {
+  uint32_t* part = nullptr;
+  size_t bytes = 0;
+  int cus = 0;
+};
+// Workgroups that share one tile's K loop: as many as find a CU (`per_cu`
+// workgroups each) beside the call's `tiles`, at most `units` of the loop's
+// pieces and what the scratch holds (`outputs` u32 a part).  1: no split.
+inline uint32_t dot_splits(uint64_t tiles, uint32_t per_cu, uint32_t units, uint64_t outputs,
+                           const DotScratch& scratch) {
+  if (!scratch.part || tiles == 0 || outputs == 0) return 1;
+  uint64_t s = uint64_t(scratch.cus) * per_cu / tiles;
+  s = s < units ? s : units;
+  const uint64_t fit = scratch.bytes / 4 / outputs;
+  s = s < fit ? s : fit;
+  return s < 1 ? 1 : uint32_t(s);
+}
+hipError_t launch_reduce_parts(const uint32_t* part, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
+                               uint16_t* mask, uint64_t ld, hipStream_t s);
 bool rot_dot_applies(uint32_t r, int kind);
 hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
                           const int8_t* b,
                           uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
-                          hipStream_t s, int kind, bool galois);
-bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask);
+                          hipStream_t s, int kind, bool galois, const DotScratch& scratch);
+bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask, int cus);
 hipError_t launch_pair_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
                            const int8_t* b, uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask,
                            uint64_t ld, hipStream_t s, bool galois);
@@ -54,7 +75,7 @@ hipError_t launch_expand_rows(const int8_t* qop, uint32_t q, const imc_row* rows
                               uint32_t rows_pad, hipStream_t s, bool galois);
 hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const int8_t* b, uint64_t first_entry,
                       uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld, hipStream_t s, int variant,
-                      bool galois);
+                      bool galois, const DotScratch& scratch);
 
 // A call's optional table of per-query ids, column counts and match buffers
 // (imc_query_entry, one per query of the launch), and the row count of the

@@ -467,14 +467,10 @@ __global__ void __launch_bounds__(kPairThreads) pair_dot_kernel(PairDotArgs args
 // waves' rows idle here), 10: 3.13 / 3.86, 18: 5.42 / 5.65, 32: 6.07 / 8.37;
 // 20,000 entries, 16: 1.37 / 1.49, 18: 1.89 / 1.81, 32: 2.12 / 2.60;
 // 1,000 entries, 48: 0.52 / 0.41.
-bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask) {
+bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask, int cus) {
   if (r < 27 || r > 31) return false;
   for (uint32_t i = 1; i < r; ++i)
     if (rot[i] != rot[0] + int(i)) return false;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    return false;
   const uint64_t cols = (n + kPairN - 1) / kPairN * (mask ? 2 : 1);
   const uint64_t mine = (uint64_t(q + kPairQ - 1) / kPairQ * cols + cus - 1) / cus;
   const uint64_t theirs = ((uint64_t(q) * r + 255) / 256 * cols + cus - 1) / cus;

@@ -33,6 +33,8 @@ struct RotDotArgs {
   uint64_t b_block0, b_blocks, n;
   uint32_t mt, nt;
   uint32_t max_q;        // query slots per tile (LDS sizing)
+  uint32_t splits, seg_per;   // split launches: workgroups per tile, segments of each
+  uint32_t* part;        // split launches: u32 [vec][split][rows][n]
   int8_t rot[IMC_MAX_ROT_DEV];
 };
 
@@ -72,12 +74,14 @@ struct RotTile {
   const int8_t* rot;
   uint64_t ld, b_block0, b_blocks, n;
   uint32_t rows, r, max_q;
+  int seg_begin, seg_end;      // SPLIT: the tile's share of the angular-row segments
+  uint32_t* part;              // SPLIT: where its sums go, u32 [rows][n]
 };
 
 // One 256 x 128 output tile (row tile u, column tile t) of vector `vec`,
-// the whole K loop and the epilogue.  LDS: 3 database stages, then the two
-// query segment buffers of max_q slots.
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
+// the whole K loop (SPLIT: some of its segments) and the epilogue.  LDS: 3
+// database stages, then the two query segment buffers of max_q slots.
+template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH, bool SPLIT = false>
 __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, uint32_t t, int vec, int8_t* lds) {
   using G = Geo<K>;
   constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N;
@@ -152,7 +156,9 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
 
   constexpr int kSteps = G::kChunks / 2;        // 800 or 400
   constexpr int kSegSteps = kRowLen / 32;    // 25 K-steps per segment
-  static_assert(kSteps % NSETS == 0, "the K loop is unrolled by NSETS");
+  static_assert((SPLIT ? kSegSteps : kSteps) % NSETS == 0, "the K loop is unrolled by NSETS");
+  const int seg_b = SPLIT ? args.seg_begin : 0, seg_e = SPLIT ? args.seg_end : kSteps / kSegSteps;
+  const int k_b = seg_b * kSegSteps, k_e = SPLIT ? seg_e * kSegSteps : kSteps;
   v4i rs[NSETS][kBPerThread];
   v4i ra[ACH];
 
@@ -196,41 +202,41 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
   }
 
   // prologue: A segment 0; B steps 0 and 1 in stages 0 and 1; steps 2.. in registers
-  IMC_ALOAD(0)
-  IMC_ASTORE(0)
+  IMC_ALOAD(seg_b)
+  IMC_ASTORE(seg_b & 1)
   {
     v4i r0[kBPerThread];
-    IMC_BLOAD(r0, 0)
-    IMC_BSTORE(r0, 0)
-    IMC_BLOAD(r0, 1)
-    IMC_BSTORE(r0, 1)
+    IMC_BLOAD(r0, k_b)
+    IMC_BSTORE(r0, k_b % 3)
+    IMC_BLOAD(r0, k_b + 1)
+    IMC_BSTORE(r0, (k_b + 1) % 3)
   }
 #pragma unroll
-  for (int set = 0; set < NSETS; ++set) { IMC_BLOAD(rs[set], set + 2) }
-  IMC_ALOAD(1)
+  for (int set = 0; set < NSETS; ++set) { IMC_BLOAD(rs[set], k_b + set + 2) }
+  IMC_ALOAD(min(seg_b + 1, seg_e - 1))
   __syncthreads();
   // a wave whose rows are all past the last row (the partial last row tile)
   // only stages operands for the others: no fragment reads, no MFMAs
   const bool live = m0 + uint32_t(wm * WM * 32) < args.rows;
   if (!live) {
-    for (int k0 = 0; k0 < kSteps; k0 += NSETS) {
+    for (int k0 = k_b; k0 < k_e; k0 += NSETS) {
 #pragma unroll
       for (int uu = 0; uu < NSETS; ++uu) {
         const int k = k0 + uu;
         const int seg = k / kSegSteps, ts = k - seg * kSegSteps;
         IMC_BSTORE(rs[uu], (k + 2) % 3)
-        if (ts == kSegSteps / 2 && seg + 1 < kSteps / kSegSteps) {
+        if (ts == kSegSteps / 2 && seg + 1 < seg_e) {
           IMC_ASTORE((seg + 1) & 1)
-          IMC_ALOAD(min(seg + 2, kSteps / kSegSteps - 1))
+          IMC_ALOAD(min(seg + 2, seg_e - 1))
         }
         __syncthreads();
-        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, kSteps - 1))
+        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, k_e - 1))
       }
     }
   } else {
-    IMC_FRAGS(falo, fahi, fblo, fbhi, 0)
+    IMC_FRAGS(falo, fahi, fblo, fbhi, k_b)
 
-    for (int k0 = 0; k0 < kSteps; k0 += NSETS) {
+    for (int k0 = k_b; k0 < k_e; k0 += NSETS) {
 #pragma unroll
       for (int uu = 0; uu < NSETS; ++uu) {
         const int k = k0 + uu;
@@ -238,7 +244,7 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
         // interleave the next step's fragment reads with this step's MFMAs
         // (the compiler's single-wave small-GEMM schedule; ~1.5 % faster here)
         __builtin_amdgcn_iglp_opt(1);
-        IMC_FRAGS(nalo, nahi, nblo, nbhi, min(k + 1, kSteps - 1))
+        IMC_FRAGS(nalo, nahi, nblo, nbhi, min(k + 1, k_e - 1))
 #pragma unroll
         for (int x = 0; x < WM; ++x)
 #pragma unroll
@@ -251,12 +257,12 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
         // mid-segment: the next segment's query bytes go to the other A buffer
         // (last read during the previous segment), then its loads are issued
         // for the segment after it.
-        if (ts == kSegSteps / 2 && seg + 1 < kSteps / kSegSteps) {
+        if (ts == kSegSteps / 2 && seg + 1 < seg_e) {
           IMC_ASTORE((seg + 1) & 1)
-          IMC_ALOAD(min(seg + 2, kSteps / kSegSteps - 1))
+          IMC_ALOAD(min(seg + 2, seg_e - 1))
         }
         __syncthreads();
-        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, kSteps - 1))
+        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, k_e - 1))
 #pragma unroll
         for (int x = 0; x < WM; ++x) { falo[x] = nalo[x]; fahi[x] = nahi[x]; }
 #pragma unroll
@@ -282,7 +288,10 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
         const uint32_t row = m0 + (wm * WM + x) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
         if (row < args.rows) {
           const uint32_t z = uint32_t(acc0[x][y][e]) + (uint32_t(acc1[x][y][e]) << 8);
-          out[uint64_t(row) * args.ld + col] = uint16_t(z);
+          if (SPLIT)
+            args.part[uint64_t(row) * args.n + col] = z;
+          else
+            out[uint64_t(row) * args.ld + col] = uint16_t(z);
         }
       }
     }
@@ -302,8 +311,33 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_kernel(RotDotA
   const uint32_t t = tg * 8 + xcd;
   if (t >= args.nt) return;
   const RotTile tile{args.qop, args.qidx, args.b, args.out[vec], args.rot, args.ld, args.b_block0, args.b_blocks,
-                     args.n, args.rows, args.r, args.max_q};
+                     args.n, args.rows, args.r, args.max_q, 0, 0, nullptr};
   rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>(tile, u, t, vec, lds);
+}
+
+// The same with a tile's segments split over args.splits workgroups, for
+// calls with fewer tiles than CUs: their time is that of one workgroup's
+// serial K loop, 0.26 us a step with one wave row live and 0.47 with all
+// (800 steps), at whatever size.  Each part's sums go to scratch as u32 and
+// reduce_parts_kernel adds them.  31 rows x 1,000 entries: 209 -> 27 us;
+// 1,984 rows x 64 entries: 394 -> 48 us; 93 rows x 4,000: 244 -> 90.
+template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_split_kernel(RotDotArgs args) {
+  using G = Geo<K>;
+  extern __shared__ __align__(16) int8_t lds[];
+  const int vec = blockIdx.z;
+  // (column tile, part) pairs take the place of column tiles in the XCD-aware order
+  const uint32_t i = blockIdx.x;
+  const uint32_t xcd = i & 7, s8 = i >> 3;
+  const uint32_t u = s8 % args.mt, tp = (s8 / args.mt) * 8 + xcd;
+  if (tp >= args.nt * args.splits) return;
+  const uint32_t t = tp / args.splits, part = tp % args.splits;
+  constexpr int kSegs = G::kChunks / 2 / (kRowLen / 32);
+  const RotTile tile{args.qop, args.qidx, args.b, nullptr, args.rot, args.ld, args.b_block0, args.b_blocks,
+                     args.n, args.rows, args.r, args.max_q, int(part * args.seg_per),
+                     min(int((part + 1) * args.seg_per), kSegs),
+                     args.part + (uint64_t(vec) * args.splits + part) * args.rows * args.n};
+  rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH, true>(tile, u, t, vec, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -349,7 +383,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_groups_kernel(
     if (!first) __syncthreads();
     first = false;
     const RotTile tile{grp.qop, nullptr, args.b, grp.out[vec], grp.rot, args.ld, args.b_block0, args.b_blocks,
-                       args.n, grp.rows, grp.r, args.max_q};
+                       args.n, grp.rows, grp.r, args.max_q, 0, 0, nullptr};
     rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>(tile, u, t, vec, lds);
   }
 }
@@ -736,7 +770,7 @@ template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
 static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
                                  const int8_t* b,
                                  uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
-                                 hipStream_t s) {
+                                 hipStream_t s, const DotScratch& scratch) {
   constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N, kThreads = 64 * WAVES_M * WAVES_N;
   const uint32_t rows = q * r;
   if (rows == 0 || n == 0) return hipSuccess;
@@ -763,6 +797,25 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   if (uint64_t(ntg) * 8 * d.mt > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const dim3 grid(ntg * 8 * d.mt, 1, mask ? 2 : 1);   // z: code, mask
   const size_t lds = 3 * size_t(kBN / 32) * 2 * 2 * 32 * 16 + 2 * size_t(d.max_q) * 2 * kSegBytes;
+  // one workgroup per CU (its LDS): split the segments while CUs are left over
+  constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / (kRowLen / 32);
+  const uint32_t splits = dot_splits(uint64_t(d.mt) * d.nt * grid.z, 1, kSegs, uint64_t(rows) * n * grid.z, scratch);
+  if (splits > 1) {
+    d.seg_per = (kSegs + splits - 1) / splits;
+    d.splits = (kSegs + d.seg_per - 1) / d.seg_per;
+    d.part = scratch.part;
+    auto kern = rot_dot_split_kernel<K, WM, WN, WAVES_M, WAVES_N, 5, ACH>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    const uint32_t ntp = (d.nt * d.splits + 7) / 8 * 8;
+    hipLaunchKernelGGL(kern, dim3(ntp * d.mt, 1, grid.z), dim3(kThreads), lds, s, d);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_reduce_parts(d.part, d.splits, rows, n, code, mask, ld, s);
+  }
+  d.splits = d.seg_per = 0;
+  d.part = nullptr;
   auto kern = rot_dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
@@ -930,7 +983,7 @@ hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const
 hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
                           const int8_t* b,
                           uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
-                          hipStream_t s, int kind, bool galois) {
+                          hipStream_t s, int kind, bool galois, const DotScratch& scratch) {
   // 0: 8 waves of 64 x 64, loads 6 steps ahead; 2: HBM -> LDS copies, 8
   // stages; 3: database fragments straight into registers
   if (galois) {
@@ -938,16 +991,16 @@ hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, u
       case 2: return launch_rot_dma<kKGalois>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
       case 3: return launch_rot_gb<kKGalois, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
       default:
-        if (r >= 22) return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
-        return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
+        if (r >= 22) return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
+        return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
     }
   }
   switch (kind) {
     case 2: return launch_rot_dma<kK>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
     case 3: return launch_rot_gb<kK, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
     default:
-      if (r >= 22) return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
-      return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
+      if (r >= 22) return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
+      return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
   }
 }
 
