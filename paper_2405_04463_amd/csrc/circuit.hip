@@ -613,86 +613,104 @@ __global__ void __launch_bounds__(256) reshare_kernel(ReshareArgs a) {
 // OR-tree (Sec. 4.2): x OR y = x ^ y ^ AND(x, y), gate i of level L uses
 // stream (DOM_OR, qid) at position (L << 40) + i/8, word i%8.
 // ---------------------------------------------------------------------------
+constexpr int kOrChunk = 1024;          // words of a subtree, ten levels
+constexpr int kOrLevels = 10;
+constexpr int kOrGates = kOrChunk - 1 + 8 * 8;   // its gates, in whole groups of 8 per level
+
 struct OrArgs {
   Keys3 keys;
   const uint64_t* in0[3];    // level 0: match[p] plane 0, [rows][mw_ld]
-  const uint64_t* in;        // levels > 0: [q][len][3]
-  uint64_t* out;             // [q][(len+1)/2][3]
-  uint64_t q, len, nw, mw_ld, in_stride, out_stride;
-  uint64_t qid_base;
-  int32_t r, level, first;
-};
-
-__global__ void __launch_bounds__(256) or_level_kernel(OrArgs a) {
-  const uint64_t half = (a.len + 1) / 2;
-  const uint64_t ng = (half + 7) / 8;
-  const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= a.q * ng) return;
-  const uint64_t qi = t / ng, g = t % ng;
-  const uint64_t stream = (uint64_t(kDomOr) << 56) | ((a.qid_base + qi) & 0xFFFFFFFFFFFFull);
-  uint32_t F[3][16];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) chacha12(a.keys.k[k], stream, (uint64_t(a.level) << 40) + g, F[k]);
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const uint64_t i = 8 * g + u;
-    if (i >= half) break;
-    B3 x, y;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const uint64_t i0 = 2 * i, i1 = 2 * i + 1;
-      if (a.first) {
-        const uint64_t r0 = i0 / a.nw, w0 = i0 % a.nw;
-        x.c[p] = a.in0[p][(qi * a.r + r0) * a.mw_ld + w0];
-        if (i1 < a.len) {
-          const uint64_t r1 = i1 / a.nw, w1 = i1 % a.nw;
-          y.c[p] = a.in0[p][(qi * a.r + r1) * a.mw_ld + w1];
-        } else {
-          y.c[p] = 0;
-        }
-      } else {
-        x.c[p] = a.in[(qi * a.in_stride + i0) * 3 + p];
-        y.c[p] = i1 < a.len ? a.in[(qi * a.in_stride + i1) * 3 + p] : 0;
-      }
-    }
-    const uint64_t f0 = uint64_t(F[0][2 * u]) | (uint64_t(F[0][2 * u + 1]) << 32);
-    const uint64_t f1 = uint64_t(F[1][2 * u]) | (uint64_t(F[1][2 * u + 1]) << 32);
-    const uint64_t f2 = uint64_t(F[2][2 * u]) | (uint64_t(F[2][2 * u + 1]) << 32);
-    const B3 z = bx(bx(x, y), band(x, y, f0, f1, f2));
-#pragma unroll
-    for (int p = 0; p < 3; ++p) a.out[(qi * a.out_stride + i) * 3 + p] = z.c[p];
-  }
-}
-
-struct OrFinalArgs {
-  Keys3 keys;
-  const uint64_t* in0[3];    // used when the tree had a single word per query
-  const uint64_t* in;        // [q][stride][3]
+  const uint64_t* in;        // later passes: [q][len][3]
+  uint64_t* out;             // [q][chunks][3], or with `last` dup
   uint8_t* dup[3];           // [2][q]
-  uint64_t q, stride, mw_ld;
+  uint64_t q, len, nw, mw_ld, chunks;
   uint64_t qid_base;
-  int32_t r, level, first;
+  int32_t r, level, first, last;
 };
 
-__global__ void __launch_bounds__(64) or_final_kernel(OrFinalArgs a) {
-  const uint64_t qi = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (qi >= a.q) return;
+// One workgroup reduces one chunk of 1,024 words of a query by ten levels: a
+// chunk starts at a multiple of 2^10, so its pairs and its odd ends are those
+// of the whole level.  The pass that holds a query in one chunk (`last`) goes
+// on to one word and folds it.  A gate's randomness depends on its level and
+// index only, so every ChaCha12 block of the chunk is drawn first, one key's
+// block per thread, and the levels follow in LDS: the tree's depth costs LDS
+// round trips instead of a launch and three serial blocks a level.
+// 64 queries x 31,744 words: 270 us over 16 launches, now 60 in two; one query
+// x 496 words: 102 us over 10, now 10 in one.
+__global__ void __launch_bounds__(256) or_chunk_kernel(OrArgs a) {
+  __shared__ uint64_t words[kOrChunk + kOrChunk / 2][3];   // the chunk, then every other level
+  __shared__ uint64_t tape[3][kOrGates];
+  __shared__ uint64_t fold[3][6];
+  const uint64_t qi = blockIdx.x / a.chunks, base = blockIdx.x % a.chunks * kOrChunk;
   const uint64_t stream = (uint64_t(kDomOr) << 56) | ((a.qid_base + qi) & 0xFFFFFFFFFFFFull);
-  B3 w;
+  const int len = int(min(a.len - base, uint64_t(kOrChunk)));
+  const int tid = threadIdx.x;
+  for (int i = tid; i < len; i += 256) {
+    const uint64_t w = base + i;
+    const uint64_t row = a.first ? w / a.nw : 0, col = w - row * a.nw;
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
-    w.c[p] = a.first ? a.in0[p][(qi * a.r) * a.mw_ld] : a.in[(qi * a.stride) * 3 + p];
+    for (int p = 0; p < 3; ++p)
+      words[i][p] = a.first ? a.in0[p][(qi * a.r + row) * a.mw_ld + col] : a.in[(qi * a.len + w) * 3 + p];
+  }
+  int levels = kOrLevels;
+  if (a.last)
+    for (levels = 0; (len - 1) >> levels; ++levels) {}
+  // level v's gates are (base >> (v + 1)) + 0 .. half - 1 of the tree, in
+  // groups of 8 to a block; groups_of(l, v): the groups of a level of l words
+  const auto groups_of = [base](int l, int v) {
+    const uint64_t g0 = base >> (v + 1);
+    return int(((g0 + (l + 1) / 2 - 1) >> 3) - (g0 >> 3)) + 1;
+  };
+  int total = 0;
+  for (int v = 0, l = len; v < levels; ++v, l = (l + 1) / 2) total += groups_of(l, v);
+  for (int it = tid; it < 3 * total; it += 256) {
+    const int k = it / total, slot = it - k * total;
+    int v = 0, l = len, g = slot;
+    for (int ng; g >= (ng = groups_of(l, v)); ++v, l = (l + 1) / 2) g -= ng;
+    uint32_t F[16];
+    chacha12(a.keys.k[k], stream, (uint64_t(a.level + v) << 40) + (base >> (v + 4)) + g, F);
 #pragma unroll
-  for (int lv = 0; lv < 6; ++lv) {
-    const int sh = 32 >> lv;
-    const int level = a.level + lv;
-    uint32_t F[3][16];
+    for (int u = 0; u < 8; ++u) tape[k][8 * slot + u] = uint64_t(F[2 * u]) | (uint64_t(F[2 * u + 1]) << 32);
+  }
+  if (a.last && tid < 18) {
+    const int k = tid / 6, v = tid % 6;
+    uint32_t F[16];
+    chacha12(a.keys.k[k], stream, uint64_t(a.level + levels + v) << 40, F);
+    fold[k][v] = uint64_t(F[0]) | (uint64_t(F[1]) << 32);
+  }
+  __syncthreads();
+  int cur = 0, l = len, groups = 0;   // this level's words start at words[cur]
+  for (int v = 0; v < levels; ++v) {
+    const int half = (l + 1) / 2, next = kOrChunk - cur;
+    for (int i = tid; i < half; i += 256) {
+      const int t = 8 * groups + int((base >> (v + 1)) & 7) + i;
+      B3 x, y;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) chacha12(a.keys.k[k], stream, uint64_t(level) << 40, F[k]);
+      for (int p = 0; p < 3; ++p) {
+        x.c[p] = words[cur + 2 * i][p];
+        y.c[p] = 2 * i + 1 < l ? words[cur + 2 * i + 1][p] : 0;
+      }
+      const B3 z = bx(bx(x, y), band(x, y, tape[0][t], tape[1][t], tape[2][t]));
+#pragma unroll
+      for (int p = 0; p < 3; ++p) words[next + i][p] = z.c[p];
+    }
+    groups += groups_of(l, v);
+    l = half;
+    cur = next;
+    __syncthreads();
+  }
+  if (tid != 0) return;
+  B3 w{{words[cur][0], words[cur][1], words[cur][2]}};
+  if (!a.last) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) a.out[uint64_t(blockIdx.x) * 3 + p] = w.c[p];
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < 6; ++v) {
+    const int sh = 32 >> v;
     const B3 y{{w.c[0] >> sh, w.c[1] >> sh, w.c[2] >> sh}};
-    w = bx(bx(w, y), band(w, y, uint64_t(F[0][0]) | (uint64_t(F[0][1]) << 32),
-                          uint64_t(F[1][0]) | (uint64_t(F[1][1]) << 32),
-                          uint64_t(F[2][0]) | (uint64_t(F[2][1]) << 32)));
+    w = bx(bx(w, y), band(w, y, fold[0][v], fold[1][v], fold[2][v]));
   }
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
@@ -894,54 +912,34 @@ size_t or_tree_ws_bytes(uint64_t q, uint64_t r, uint64_t nw) {
 hipError_t launch_or_tree(const Keys3& keys, const uint64_t* const match[3], uint64_t q, uint64_t nw, uint64_t mw_ld,
                           const imc_ids_dev& ids, void* ws, uint8_t* const dup[3], hipStream_t s) {
   if (q == 0) return hipSuccess;
-  const uint64_t len0 = uint64_t(ids.r) * nw;
-  const uint64_t stride = (len0 + 1) / 2;
-  uint64_t* buf[2] = {reinterpret_cast<uint64_t*>(ws), reinterpret_cast<uint64_t*>(ws) + q * stride * 3};
-  uint64_t len = len0;
-  int level = 0, cur = -1;
-  while (len > 1) {
+  uint64_t len = uint64_t(ids.r) * nw;
+  // pass i writes q * ceil(len / 1024^i) words: the two halves of ws in turn
+  uint64_t* buf[2] = {reinterpret_cast<uint64_t*>(ws), reinterpret_cast<uint64_t*>(ws) + q * ((len + 1) / 2) * 3};
+  for (int pass = 0;; ++pass) {
     OrArgs a;
     a.keys = keys;
-    for (int p = 0; p < 3; ++p) a.in0[p] = match[p];
-    a.in = cur >= 0 ? buf[cur] : nullptr;
-    a.out = buf[cur >= 0 ? 1 - cur : 0];
+    for (int p = 0; p < 3; ++p) {
+      a.in0[p] = match[p];
+      a.dup[p] = dup[p];
+    }
+    a.in = pass ? buf[(pass - 1) & 1] : nullptr;
+    a.out = buf[pass & 1];
     a.q = q;
     a.len = len;
     a.nw = nw;
     a.mw_ld = mw_ld;
-    a.in_stride = stride;
-    a.out_stride = stride;
+    a.chunks = (len + kOrChunk - 1) / kOrChunk;
     a.qid_base = ids.query_id_base;
     a.r = ids.r;
-    a.level = level;
-    a.first = cur < 0;
-    const uint64_t half = (len + 1) / 2;
-    const uint64_t threads = q * ((half + 7) / 8);
-    if (!fits_grid(threads, 256)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(or_level_kernel, dim3(unsigned((threads + 255) / 256)), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    cur = cur >= 0 ? 1 - cur : 0;
-    len = half;
-    ++level;
+    a.level = pass * kOrLevels;
+    a.first = pass == 0;
+    a.last = a.chunks == 1;
+    if (q > 0x7FFFFFFFull / a.chunks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(or_chunk_kernel, dim3(unsigned(q * a.chunks)), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.last) return e;
+    len = a.chunks;
   }
-  OrFinalArgs f;
-  f.keys = keys;
-  for (int p = 0; p < 3; ++p) {
-    f.in0[p] = match[p];
-    f.dup[p] = dup[p];
-  }
-  f.in = cur >= 0 ? buf[cur] : nullptr;
-  f.q = q;
-  f.stride = stride;
-  f.mw_ld = mw_ld;
-  f.qid_base = ids.query_id_base;
-  f.r = ids.r;
-  f.level = level;
-  f.first = cur < 0;
-  if (!fits_grid(q, 64)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(or_final_kernel, dim3(unsigned((q + 63) / 64)), dim3(64), 0, s, f);
-  return hipGetLastError();
 }
 
 __global__ void zero_counter_kernel(unsigned long long* c) { *c = 0ull; }
