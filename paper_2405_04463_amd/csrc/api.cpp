@@ -164,30 +164,21 @@ imc_status imc_create(const imc_params* p, int device, imc_ctx** out) {
   c->max_rows = p->max_rows;
   c->dot_variant = int(p->flags & 0x1Fu);
   c->rot_op_bytes = blocks_for(p->max_rows) * imc::kBlockBytes;
-  if (hipMalloc(reinterpret_cast<void**>(&c->rot_op), c->rot_op_bytes) != hipSuccess) {
+  // one allocation: the rotated operand, the parts of split dot products, the counter
+  if (hipMalloc(reinterpret_cast<void**>(&c->rot_op), c->rot_op_bytes + kPartBytes + sizeof(unsigned long long)) !=
+      hipSuccess) {
     delete c;
     return IMC_ENOMEM;
   }
-  if (hipMalloc(reinterpret_cast<void**>(&c->bad), sizeof(unsigned long long)) != hipSuccess) {
-    (void)hipFree(c->rot_op);
-    delete c;
-    return IMC_ENOMEM;
-  }
-  if (hipMalloc(reinterpret_cast<void**>(&c->parts.part), kPartBytes) != hipSuccess) {
-    (void)hipFree(c->rot_op);
-    (void)hipFree(c->bad);
-    delete c;
-    return IMC_ENOMEM;
-  }
+  c->parts.part = reinterpret_cast<uint32_t*>(c->rot_op + c->rot_op_bytes);
   c->parts.bytes = kPartBytes;
+  c->bad = reinterpret_cast<unsigned long long*>(c->rot_op + c->rot_op_bytes + kPartBytes);
   imc_status rs = resolve_scratch(device);   // the device is current (guard above)
   if (rs == IMC_OK &&
       hipDeviceGetAttribute(&c->parts.cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
     rs = IMC_EDEVICE;
   if (rs != IMC_OK) {
     (void)hipFree(c->rot_op);
-    (void)hipFree(c->bad);
-    (void)hipFree(c->parts.part);
     delete c;
     return rs;
   }
@@ -200,8 +191,6 @@ void imc_destroy(imc_ctx* c) {
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
   (void)hipFree(c->rot_op);
-  (void)hipFree(c->bad);
-  (void)hipFree(c->parts.part);
   delete c;
 }
 
@@ -271,16 +260,14 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
   const bool rot_tiles = tiles == IMC_DOT_TILES_AUTO || tiles == IMC_DOT_TILES_ROTATION ||
                          tiles == IMC_DOT_TILES_ROTATION_LDSCOPY || tiles == IMC_DOT_TILES_ROTATION_DIRECT;
   const int kind = tiles == IMC_DOT_TILES_ROTATION_LDSCOPY ? 2 : tiles == IMC_DOT_TILES_ROTATION_DIRECT ? 3 : 0;
-  if (tiles == IMC_DOT_TILES_AUTO &&
-      imc::pair_dot_applies(uint32_t(q), uint32_t(ids->r), ids->rot, n, mask_dot != nullptr, c->parts.cus))
-    return dev_status(imc::launch_pair_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r),
-                                           ids->rot, static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot,
-                                           mask_dot, ld, hipStream_t(stream), galois));
   if (rot_tiles && imc::rot_dot_applies(uint32_t(ids->r), kind)) {
     // rotations read straight from the unrotated operand staged in LDS
-    return dev_status(imc::launch_rot_dot(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
-                                          static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot, mask_dot,
-                                          ld, hipStream_t(stream), kind, galois, parts_for(c, hipStream_t(stream))));
+    const imc::RotCall call{static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
+                            static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot, mask_dot, ld};
+    const imc::DotScratch parts = parts_for(c, hipStream_t(stream));
+    return dev_status(tiles == IMC_DOT_TILES_AUTO
+                          ? imc::launch_rotations(call, hipStream_t(stream), galois, parts)
+                          : imc::launch_rot_dot(call, hipStream_t(stream), kind, galois, parts));
   }
   const uint32_t rows_pad = uint32_t(blocks_for(rows) * 32);
   hipError_t e = imc::launch_expand(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,

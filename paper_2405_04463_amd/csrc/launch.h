@@ -53,14 +53,22 @@ inline uint32_t dot_splits(uint64_t tiles, uint32_t per_cu, uint32_t units, uint
 hipError_t launch_reduce_parts(const uint32_t* part, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
                                uint16_t* mask, uint64_t ld, hipStream_t s);
 bool rot_dot_applies(uint32_t r, int kind);
-hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
-                          const int8_t* b,
-                          uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
-                          hipStream_t s, int kind, bool galois, const DotScratch& scratch);
-bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask, int cus);
-hipError_t launch_pair_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
-                           const int8_t* b, uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask,
-                           uint64_t ld, hipStream_t s, bool galois);
+// One dot call at r >= 13 rotations: q queries (rows of qop, or those that
+// qidx names) against n entries from first_entry on.
+struct RotCall {
+  const int8_t* qop;
+  const uint32_t* qidx;
+  uint32_t q, r;
+  const int8_t* rot;
+  const int8_t* b;
+  uint64_t first_entry, n;
+  uint16_t* code;
+  uint16_t* mask;   // null: the code dot alone
+  uint64_t ld;
+};
+hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch);
+// The same with the kernel, or the kernels, chosen for the call's sizes.
+hipError_t launch_rotations(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch);
 // One query group of a fused rotation-aware launch (imc_dot_shares_groups).
 struct DotGroup {
   const int8_t* qop;

@@ -459,24 +459,6 @@ __global__ void __launch_bounds__(kPairThreads) pair_dot_kernel(PairDotArgs args
   }
 }
 
-// Consecutive ascending rotations in a number that fills the 4 x 4 pairs, and
-// enough tiles.  A tile here (16 queries) takes 1.43 times one of rot_dot.hip
-// (256 rows, about 8 queries), and a call takes its tiles in rounds of one
-// per CU: the pairs are taken when their rounds are the shorter.  Measured,
-// ms pairs / rot_dot.hip: 65,536 entries, 8 queries 2.65 / 2.36 (one of two
-// waves' rows idle here), 10: 3.13 / 3.86, 18: 5.42 / 5.65, 32: 6.07 / 8.37;
-// 20,000 entries, 16: 1.37 / 1.49, 18: 1.89 / 1.81, 32: 2.12 / 2.60;
-// 1,000 entries, 48: 0.52 / 0.41.
-bool pair_dot_applies(uint32_t q, uint32_t r, const int8_t* rot, uint64_t n, bool mask, int cus) {
-  if (r < 27 || r > 31) return false;
-  for (uint32_t i = 1; i < r; ++i)
-    if (rot[i] != rot[0] + int(i)) return false;
-  const uint64_t cols = (n + kPairN - 1) / kPairN * (mask ? 2 : 1);
-  const uint64_t mine = (uint64_t(q + kPairQ - 1) / kPairQ * cols + cus - 1) / cus;
-  const uint64_t theirs = ((uint64_t(q) * r + 255) / 256 * cols + cus - 1) / cus;
-  return 10 * mine < 7 * theirs;
-}
-
 template <int K>
 static hipError_t launch_pair_k(PairDotArgs d, bool mask, hipStream_t s) {
   d.mt = (d.q + kPairQ - 1) / kPairQ;
@@ -491,26 +473,147 @@ static hipError_t launch_pair_k(PairDotArgs d, bool mask, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pair_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
-                           const int8_t* b, uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask,
-                           uint64_t ld, hipStream_t s, bool galois) {
-  if (q == 0 || n == 0) return hipSuccess;
-  if (r < 27 || r > 31) return hipErrorInvalidValue;
+static hipError_t launch_pair(const RotCall& c, hipStream_t s, bool galois) {
   PairDotArgs d;
-  d.qop = qop;
-  d.qidx = qidx;
-  d.b = b;
-  d.out[0] = code;
-  d.out[1] = mask;
-  d.ld = ld;
-  d.q = q;
-  d.r = r;
-  d.s0 = rot[0];
-  d.b_block0 = first_entry / 32;
-  d.b_blocks = (n + 31) / 32;
-  d.n = n;
+  d.qop = c.qop;
+  d.qidx = c.qidx;
+  d.b = c.b;
+  d.out[0] = c.code;
+  d.out[1] = c.mask;
+  d.ld = c.ld;
+  d.q = c.q;
+  d.r = c.r;
+  d.s0 = c.rot[0];
+  d.b_block0 = c.first_entry / 32;
+  d.b_blocks = (c.n + 31) / 32;
+  d.n = c.n;
   d.mt = d.nt = 0;
-  return galois ? launch_pair_k<kKGalois>(d, mask != nullptr, s) : launch_pair_k<kK>(d, mask != nullptr, s);
+  return galois ? launch_pair_k<kKGalois>(d, c.mask != nullptr, s) : launch_pair_k<kK>(d, c.mask != nullptr, s);
+}
+
+// ---------------------------------------------------------------------------
+// Which kernel takes what of a call at r >= 13 rotations.  Times are counted
+// in units of 5 us of the replicated form.  A call takes its tiles in rounds
+// of one per CU; a tile's time, from 65,536 entries (ms / rounds): rot_dot.hip
+// 2 queries 1.15 / 4, 4: 1.48 / 4, 6: 2.05 / 4, 8: 2.36 / 4 (one row tile: the
+// database bounds it, waves without rows are idle), 16: 4.35 / 8, 64: 15.8 /
+// 32; pairs 8 queries 2.65 / 4, 10: 3.13 / 4, 16: 3.50 / 4 (one query tile),
+// 18: 5.42 / 8, 32: 6.07 / 8, 64: 11.2 / 16.  The last round is rarely full,
+// and up to 8 queries past a multiple of 16 leave half of a pairs' tile idle:
+// those columns and those queries may go to rot_dot.hip's kernel in calls of
+// their own, which splits its loop when its tiles are few.  us, one launch /
+// as planned: 16 queries x 20,011 entries 1,370 / 1,115, 18 x 65,536 5,420 /
+// 4,480, 7 queries x 15 rotations x 20,000 585 / 480.
+// ---------------------------------------------------------------------------
+constexpr uint64_t kLaunchCost = 2;
+
+static uint64_t rot_tile_cost(uint64_t rows) { return rows > 256 ? 104 : 40 + 20 * ((rows + 63) / 64); }
+static uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 145 : q > 8 ? 172 : 132; }
+
+static uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
+  if (q == 0 || n == 0) return 0;
+  const uint64_t tiles = (q * r + 255) / 256 * ((n + kPairN - 1) / kPairN) * vecs;
+  const uint32_t splits = dot_splits(tiles, 1, 16, q * r * n * vecs, scratch);
+  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(q * r) / splits + 2;
+  return kLaunchCost + rot_tile_cost(q * r) * ((tiles + scratch.cus - 1) / scratch.cus);
+}
+
+// Column tiles that fill whole rounds, `per` tiles each.
+static uint64_t full_cols(uint64_t n, uint64_t per, const DotScratch& scratch) {
+  return scratch.cus > 0 ? (n + kPairN - 1) / kPairN * per / scratch.cus * scratch.cus / per : 0;
+}
+
+// rot_dot.hip's columns that go in a first call, the whole rounds; all n of
+// them if the last round is better not taken apart.
+static uint64_t rot_first_cols(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
+  const uint64_t m = full_cols(n, (q * r + 255) / 256 * vecs, scratch) * kPairN;
+  if (m == 0 || m >= n) return n;
+  return rot_cost(q, r, m, vecs, scratch) + rot_cost(q, r, n - m, vecs, scratch) < rot_cost(q, r, n, vecs, scratch)
+             ? m
+             : n;
+}
+
+static uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
+  if (q == 0 || n == 0) return 0;
+  const uint64_t m = rot_first_cols(q, r, n, vecs, scratch);
+  return rot_cost(q, r, m, vecs, scratch) + rot_cost(q, r, n - m, vecs, scratch);
+}
+
+struct RotPlan {
+  uint32_t q;   // queries and columns of the pairs; the rest is rot_dot.hip's
+  uint64_t n;
+};
+
+static RotPlan rot_plan(const RotCall& c, const DotScratch& scratch) {
+  const RotPlan none{0, 0};
+  if (c.r < 27 || c.r > 31 || scratch.cus <= 0) return none;
+  for (uint32_t i = 1; i < c.r; ++i)
+    if (c.rot[i] != c.rot[0] + int(i)) return none;   // consecutive, ascending
+  const uint32_t vecs = c.mask ? 2 : 1;
+  RotPlan best = none;
+  uint64_t least = rot_rounds_cost(c.q, c.r, c.n, vecs, scratch);
+  const uint32_t over = c.q % kPairQ;
+  for (int less = 0; less < 2; ++less) {
+    if (less && (over == 0 || over > kPairQ / 2)) break;
+    const uint32_t q = less ? c.q - over : c.q;
+    if (q == 0) break;
+    const uint64_t per = uint64_t(q + kPairQ - 1) / kPairQ * vecs, nt = (c.n + kPairN - 1) / kPairN;
+    const uint64_t full = full_cols(c.n, per, scratch);
+    for (int part = 0; part < 2; ++part) {
+      const uint64_t cols = part ? full : nt;
+      if (cols == 0 || (part && cols == nt)) break;
+      const uint64_t n = cols * kPairN < c.n ? cols * kPairN : c.n;
+      const uint64_t cost = kLaunchCost + pair_tile_cost(q) * ((cols * per + scratch.cus - 1) / scratch.cus) +
+                            rot_rounds_cost(q, c.r, c.n - n, vecs, scratch) +
+                            rot_rounds_cost(c.q - q, c.r, c.n, vecs, scratch);
+      if (cost < least) {
+        least = cost;
+        best = RotPlan{q, n};
+      }
+    }
+  }
+  return best;
+}
+
+// The call's columns from `from` on.
+static RotCall columns_from(RotCall c, uint64_t from) {
+  c.first_entry += from;
+  c.n -= from;
+  c.code += from;
+  if (c.mask) c.mask += from;
+  return c;
+}
+
+static hipError_t launch_rot_rounds(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch) {
+  RotCall first = c;
+  first.n = scratch.cus > 0 ? rot_first_cols(c.q, c.r, c.n, c.mask ? 2 : 1, scratch) : c.n;
+  const hipError_t e = launch_rot_dot(first, s, 0, galois, scratch);
+  return e != hipSuccess || first.n == c.n ? e : launch_rot_dot(columns_from(c, first.n), s, 0, galois, scratch);
+}
+
+hipError_t launch_rotations(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch) {
+  if (c.q == 0 || c.n == 0) return hipSuccess;
+  const RotPlan p = rot_plan(c, scratch);
+  if (p.n == 0) return launch_rot_rounds(c, s, galois, scratch);
+  RotCall main = c;
+  main.q = p.q;
+  const RotCall right = columns_from(main, p.n);
+  main.n = p.n;
+  hipError_t e = launch_pair(main, s, galois);
+  if (e == hipSuccess && right.n) e = launch_rot_rounds(right, s, galois, scratch);
+  if (e == hipSuccess && p.q < c.q) {
+    RotCall below = c;
+    below.q = c.q - p.q;
+    if (c.qidx)
+      below.qidx += p.q;
+    else
+      below.qop += size_t(p.q) * (galois ? Geo<kKGalois>::kQopRowBytes : Geo<kK>::kQopRowBytes);
+    const uint64_t off = uint64_t(p.q) * c.r * c.ld;
+    below.code += off;
+    if (below.mask) below.mask += off;
+    e = launch_rot_rounds(below, s, galois, scratch);
+  }
+  return e;
 }
 
 }  // namespace imc

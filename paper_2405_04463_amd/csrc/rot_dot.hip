@@ -980,27 +980,24 @@ hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const
                     : launch_rot_groups_cfg<kK, 5>(groups, ngroups, b, first_entry, n, ld, persistent, s);
 }
 
-hipError_t launch_rot_dot(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
-                          const int8_t* b,
-                          uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
-                          hipStream_t s, int kind, bool galois, const DotScratch& scratch) {
+hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch) {
   // 0: 8 waves of 64 x 64, loads 6 steps ahead; 2: HBM -> LDS copies, 8
   // stages; 3: database fragments straight into registers
   if (galois) {
     switch (kind) {
-      case 2: return launch_rot_dma<kKGalois>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
-      case 3: return launch_rot_gb<kKGalois, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
+      case 2: return launch_rot_dma<kKGalois>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
+      case 3: return launch_rot_gb<kKGalois, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
       default:
-        if (r >= 22) return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
-        return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
+        if (c.r >= 22) return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+        return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
     }
   }
   switch (kind) {
-    case 2: return launch_rot_dma<kK>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
-    case 3: return launch_rot_gb<kK, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s);
+    case 2: return launch_rot_dma<kK>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
+    case 3: return launch_rot_gb<kK, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
     default:
-      if (r >= 22) return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 3>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
-      return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 5>(qop, qidx, q, r, rot, b, first_entry, n, code, mask, ld, s, scratch);
+      if (c.r >= 22) return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+      return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
   }
 }
 

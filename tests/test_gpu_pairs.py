@@ -2,8 +2,9 @@
 27..31 rotations with enough tiles) against the expanded kernel, all outputs,
 and against the oracle's local dots on the first, last and a middle entry:
 partial query tiles, ragged entry tiles, each rotation count, lists that start
-anywhere, gathered queries, a code dot alone, both sharings.  Sizes are the
-smallest ones at which the call takes this kernel."""
+anywhere, gathered queries, a code dot alone, both sharings, and calls whose
+last columns or last queries go to the rotation kernel.  Sizes are about the
+smallest at which a call on 256 CUs takes this kernel."""
 import numpy as np
 import pytest
 
@@ -19,11 +20,12 @@ def dev64(a):
 
 
 @pytest.mark.parametrize("q,n,first,rot,galois,mask,gather", [
-    (10, 8321, 64, range(-15, 16), False, True, False),     # one query tile of 10, one entry in the last tile
-    (16, 8449, 0, range(-13, 16), True, True, False),       # 29 rotations ending at 15, full query tile
-    (33, 4219, 128, range(-15, 15), False, True, False),    # 30 rotations, one query in the last tile
-    (20, 10977, 0, range(-11, 16), False, False, False),    # 27 rotations, code dot alone
-    (12, 8255, 0, range(-14, 14), True, True, True),        # 28 rotations, gathered queries with a repeat
+    (10, 16300, 64, range(-15, 16), False, True, False),    # one query tile of 10, ragged last entry tile
+    (16, 16385, 0, range(-13, 16), True, True, False),      # 29 rotations ending at 15; the last entry goes apart
+    (33, 8170, 128, range(-15, 15), False, True, False),    # 30 rotations; the last query goes apart
+    (20, 16390, 0, range(-14, 14), True, True, True),       # 28, gathered with a repeat; both go apart
+    (40, 10877, 0, range(-11, 16), False, False, False),    # 27 rotations, code dot alone
+    (12, 16200, 0, range(-15, 16), True, True, True),       # gathered
 ])
 def test_pairs_against_expanded_and_oracle(keys, q, n, first, rot, galois, mask, gather):
     if not torch.cuda.is_available():
