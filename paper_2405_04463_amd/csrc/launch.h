@@ -67,6 +67,9 @@ struct RotCall {
   uint64_t ld;
 };
 hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch);
+// Row tiles of such a launch that are walked column tile by column tile; a
+// last one that is not of them follows.
+uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles);
 // The same with the kernel, or the kernels, chosen for the call's sizes.
 hipError_t launch_rotations(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch);
 // One query group of a fused rotation-aware launch (imc_dot_shares_groups).

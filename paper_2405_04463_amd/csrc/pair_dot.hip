@@ -495,27 +495,32 @@ static hipError_t launch_pair(const RotCall& c, hipStream_t s, bool galois) {
 // Which kernel takes what of a call at r >= 13 rotations.  Times are counted
 // in units of 5 us of the replicated form.  A call takes its tiles in rounds
 // of one per CU; a tile's time, from 65,536 entries (ms / rounds): rot_dot.hip
-// 2 queries 1.15 / 4, 4: 1.48 / 4, 6: 2.05 / 4, 8: 2.36 / 4 (one row tile: the
-// database bounds it, waves without rows are idle), 16: 4.35 / 8, 64: 15.8 /
-// 32; pairs 8 queries 2.65 / 4, 10: 3.13 / 4, 16: 3.50 / 4 (one query tile),
-// 18: 5.42 / 8, 32: 6.07 / 8, 64: 11.2 / 16.  The last round is rarely full,
-// and up to 8 queries past a multiple of 16 leave half of a pairs' tile idle:
-// those columns and those queries may go to rot_dot.hip's kernel in calls of
-// their own, which splits its loop when its tiles are few.  us, one launch /
-// as planned: 16 queries x 20,011 entries 1,370 / 1,115, 18 x 65,536 5,420 /
-// 4,480, 7 queries x 15 rotations x 20,000 585 / 480.
+// 2 queries 1.14 / 4, 4: 1.42 / 4, 6: 1.75 / 4, 8: 2.11 / 4 (one row tile), 16:
+// 3.90 / 8, 32: 7.45 / 16, 64: 14.5 / 32; pairs 8 queries 2.65 / 4, 10: 3.06 /
+// 4, 12: 3.06 / 4, 16: 3.39 / 4 (one query tile), 32: 5.86 / 8, 64: 10.9 / 16.
+// The last round is rarely full, and up to 8 queries past a multiple of 16
+// leave half of a pairs' tile idle: those columns and those queries may go to
+// rot_dot.hip's kernel in calls of their own, which splits its loop when its
+// tiles are few.  us, one launch / as planned: 16 queries x 20,011 entries
+// 1,370 / 1,097, 18 x 65,536 5,420 / 4,490, 7 queries x 15 rotations x 20,000
+// 585 / 480.
 // ---------------------------------------------------------------------------
 constexpr uint64_t kLaunchCost = 2;
 
-static uint64_t rot_tile_cost(uint64_t rows) { return rows > 256 ? 104 : 40 + 20 * ((rows + 63) / 64); }
-static uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 145 : q > 8 ? 172 : 132; }
+// A rot_dot.hip tile alone in its columns, and beside others.
+static uint64_t rot_tile_cost(uint64_t rows) { return rows <= 64 ? 56 : rows <= 128 ? 68 : rows <= 192 ? 86 : 105; }
+constexpr uint64_t kRotSharedCost = 94;
+static uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 142 : q > 12 ? 168 : q > 8 ? 153 : 132; }
 
 static uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
   if (q == 0 || n == 0) return 0;
-  const uint64_t tiles = (q * r + 255) / 256 * ((n + kPairN - 1) / kPairN) * vecs;
-  const uint32_t splits = dot_splits(tiles, 1, 16, q * r * n * vecs, scratch);
-  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(q * r) / splits + 2;
-  return kLaunchCost + rot_tile_cost(q * r) * ((tiles + scratch.cus - 1) / scratch.cus);
+  const uint64_t rows = q * r, mt = (rows + 255) / 256, cols = (n + kPairN - 1) / kPairN * vecs;
+  const uint32_t splits = dot_splits(mt * cols, 1, 16, rows * n * vecs, scratch);
+  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / splits + 2;
+  const auto rounds = [&](uint64_t tiles) { return (tiles + scratch.cus - 1) / scratch.cus; };
+  const uint64_t lead = rot_lead_tiles(rows, mt * cols);
+  return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +
+         (lead < mt ? rot_tile_cost(rows - lead * 256) * rounds(cols) : 0);
 }
 
 // Column tiles that fill whole rounds, `per` tiles each.

@@ -22,6 +22,17 @@ namespace imc {
 // database operand streams through LDS per K-step.  Query segments are loaded
 // into registers one segment ahead and written into the other of two LDS
 // buffers half-way through the current segment.
+//
+// What bounds it: power (and up to 64 rows, memory).  On random bytes a
+// register-only loop of 16 x 16 x 64 MFMAs runs at 4.0 POP/s on this part, one
+// of 32 x 32 x 32 at 3.35; with the staging and the LDS reads the clock is at
+// 1.5 - 2.0 GHz and the MFMA pipes 0.46 - 0.57 busy.  One party's dots against
+// 65,536 entries, ms, with 32 x 32 x 32 MFMAs and 64 rows per wave at any row
+// count / as it stands: 1 query of 31 rotations 1.21 / 1.08 (5.7 GB/ms), 4:
+// 1.52 / 1.42, 8: 2.32 / 2.11, 16 of 15: 2.39 / 2.18, 40 of 15: 5.95 / 5.39,
+// 64 of 15: 8.16 / 7.71, 64 of 24: 12.2 / 11.1.  Scheduling groups that spread
+// the LDS reads over the MFMAs, and slot strides that keep two queries' rows
+// in different banks, change nothing.
 // ---------------------------------------------------------------------------
 struct RotDotArgs {
   const int8_t* qop;     // unrotated query operand, row-major [q][plane 4][K]
@@ -32,6 +43,7 @@ struct RotDotArgs {
   uint32_t rows, q, r;
   uint64_t b_block0, b_blocks, n;
   uint32_t mt, nt;
+  uint32_t lead;         // row tiles that share their column tiles' order; the last one follows if it is not of them
   uint32_t max_q;        // query slots per tile (LDS sizing)
   uint32_t splits, seg_per;   // split launches: workgroups per tile, segments of each
   uint32_t* part;        // split launches: u32 [vec][split][rows][n]
@@ -79,55 +91,68 @@ struct RotTile {
 };
 
 // One 256 x 128 output tile (row tile u, column tile t) of vector `vec`,
-// the whole K loop (SPLIT: some of its segments) and the epilogue.  LDS: 3
-// database stages, then the two query segment buffers of max_q slots.
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH, bool SPLIT = false>
-__device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, uint32_t t, int vec, int8_t* lds) {
+// the whole K loop (SPLIT: some of its segments) and the epilogue: 8 waves of
+// 64 x 64.  LDS: 3 database stages, then the two query segment buffers of
+// max_q slots.
+//
+// A K-step is two of the 32-byte database steps (64 bytes of k), one
+// 16 x 16 x 64 MFMA for each product of 16 rows and 16 entries.  A segment is
+// 25 of the half-steps, so every second segment starts with the second half of
+// a K-step: each lane takes its half's query bytes from the buffer and offset
+// of that half's segment.
+constexpr int kRotM = 256, kRotN = 128, kRotThreads = 512;
+constexpr int kRotStage = kRotN * 128;                         // one K-step: 2 limbs x 64 B per entry
+constexpr int kSegSteps = kRowLen / 32;                        // 25 half-steps per segment
+
+template <int K, int ACH, int NX, bool SPLIT>
+__device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, uint32_t t, int vec, int8_t* lds) {
   using G = Geo<K>;
-  constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N;
-  constexpr int kThreads = 64 * WAVES_M * WAVES_N;
-  constexpr int kBBlk = kBN / 32;
-  constexpr int kBChunks = kBBlk * 2 * 2 * 32;                 // per K-step
-  constexpr int kBPerThread = kBChunks / kThreads;
-  constexpr int kBStage = kBChunks * 16;
-  static_assert(kBChunks % kThreads == 0, "B chunks must divide evenly");
-  int8_t* bst = lds;                                           // 3 B stages
-  int8_t* ast = lds + 3 * kBStage;                             // 2 A segment buffers
+  constexpr int kHalves = G::kChunks / 2;                      // 800 or 400
+  static_assert(kHalves % 4 == 0, "two K-steps per turn of the loop");
+  int8_t* ast = lds + 3 * kRotStage;                           // 2 A segment buffers
   const uint32_t abuf = args.max_q * 2 * kSegBytes;            // bytes per A buffer
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
 
-  const uint32_t m0 = u * kBM;
+  const uint32_t m0 = u * kRotM;
   const uint32_t q_lo = m0 / args.r;
-  const uint32_t last_row = min(m0 + kBM, args.rows) - 1;
+  const uint32_t last_row = min(m0 + kRotM, args.rows) - 1;
   const uint32_t nq = last_row / args.r - q_lo + 1;            // <= max_q
 
-  // Per-lane A fragment offsets (bytes into an A buffer) for its row-blocks.
-  int a_off[WM];
+  const int seg_b = SPLIT ? args.seg_begin : 0, seg_e = SPLIT ? args.seg_end : kHalves / kSegSteps;
+  const int k_b = seg_b * kSegSteps, k_e = seg_e * kSegSteps;  // in half-steps
+  // a split part's last turn may reach past its end: zeros there
+  const int steps = SPLIT ? (k_e - k_b + 3) / 4 * 2 : kHalves / 2;
+
+  // Per-lane A fragment offsets (bytes into an A buffer) for its four 16-row blocks.
+  int a_off[NX];
 #pragma unroll
-  for (int x = 0; x < WM; ++x) {
-    const uint32_t row = m0 + (wm * WM + x) * 32 + (lane & 31);
+  for (int x = 0; x < NX; ++x) {
+    const uint32_t row = m0 + (wm * NX + x) * 16 + (lane & 15);
     int slot = 0, sft = 0;
     if (row < args.rows) {
       slot = int(row / args.r - q_lo);
       sft = 4 * args.rot[row % args.r];
     }
-    a_off[x] = slot * 2 * kSegBytes + kSegPad - sft + 16 * (lane >> 5);
+    a_off[x] = slot * 2 * kSegBytes + kSegPad - sft + 16 * ((lane >> 4) & 1);
   }
+  const bool second = (lane & 32) != 0;                        // this lane's half of a K-step
 
-  // B staging sources (database tile), as in dot_kernel.
-  const int8_t* bsrc[kBPerThread];
+  // B staging: a wave copies one limb of one half-step, two 32-entry blocks
+  const int b_half = wave & 1, b_limb = (wave >> 1) & 1;
+  const int8_t* bsrc[2];
+  uint32_t bdst[2];
 #pragma unroll
-  for (int j = 0; j < kBPerThread; ++j) {
-    const int c = tid + j * kThreads;
-    const int blk = c >> 7, rem = c & 127;
-    const int plane = rem >> 6, kcl = (rem >> 5) & 1, slot = rem & 31;
-    uint64_t cb = uint64_t(t) * kBBlk + blk;
+  for (int j = 0; j < 2; ++j) {
+    const int blk = (wave >> 2) + 2 * j, slot = lane & 31;
+    uint64_t cb = uint64_t(t) * (kRotN / 32) + blk;
     cb = cb < args.b_blocks ? cb : args.b_blocks - 1;
-    bsrc[j] = args.b + size_t(args.b_block0 + cb) * G::kBlockBytes + size_t(2 * vec + plane) * G::kPlaneBlockBytes +
-              size_t(kcl) * 512 + slot * 16;
+    bsrc[j] = args.b + size_t(args.b_block0 + cb) * G::kBlockBytes + size_t(2 * vec + b_limb) * G::kPlaneBlockBytes +
+              lane * 16;
+    bdst[j] = uint32_t(((blk * 2 + (slot >> 4)) * 2 + b_limb) * 1024 + (b_half * 2 + (lane >> 5)) * 256 +
+                       (slot & 15) * 16);
   }
   // A staging: chunk c of a segment buffer = (query slot, plane, 16-byte piece).
   const int a_chunks = int(nq) * 2 * kSegChunks;
@@ -135,7 +160,7 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
   int adst[ACH];
 #pragma unroll
   for (int j = 0; j < ACH; ++j) {
-    int c = tid + j * kThreads;
+    int c = tid + j * kRotThreads;
     const bool ok = c < a_chunks;
     c = ok ? c : 0;
     const int qs = c / (2 * kSegChunks), rem = c % (2 * kSegChunks);
@@ -146,28 +171,24 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
     adst[j] = ok ? (qs * 2 * kSegBytes + pl * kSegBytes + piece * 16) : -1;
   }
 
-  v16i acc0[WM][WN], acc1[WM][WN];
+  v4i acc0[NX][4], acc1[NX][4];
 #pragma unroll
-  for (int x = 0; x < WM; ++x)
-#pragma unroll
-    for (int y = 0; y < WN; ++y)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { acc0[x][y][e] = 0; acc1[x][y][e] = 0; }
+  for (int i = 0; i < 4 * NX; ++i) acc0[i >> 2][i & 3] = acc1[i >> 2][i & 3] = v4i{0, 0, 0, 0};
 
-  constexpr int kSteps = G::kChunks / 2;        // 800 or 400
-  constexpr int kSegSteps = kRowLen / 32;    // 25 K-steps per segment
-  static_assert((SPLIT ? kSegSteps : kSteps) % NSETS == 0, "the K loop is unrolled by NSETS");
-  const int seg_b = SPLIT ? args.seg_begin : 0, seg_e = SPLIT ? args.seg_end : kSteps / kSegSteps;
-  const int k_b = seg_b * kSegSteps, k_e = SPLIT ? seg_e * kSegSteps : kSteps;
-  v4i rs[NSETS][kBPerThread];
+  v4i rs[2][2];     // database bytes in flight: step j in set j % 2
   v4i ra[ACH];
-
-#define IMC_BLOAD(R, KS)                                                              \
-  _Pragma("unroll") for (int c_ = 0; c_ < kBPerThread; ++c_)                          \
-      R[c_] = *reinterpret_cast<const v4i*>(bsrc[c_] + size_t(2 * (KS)) * 512);
-#define IMC_BSTORE(R, STAGE)                                                          \
-  _Pragma("unroll") for (int c_ = 0; c_ < kBPerThread; ++c_)                          \
-      *reinterpret_cast<v4i*>(bst + (STAGE) * kBStage + (tid + c_ * kThreads) * 16) = R[c_];
+#define IMC_BLOAD(SET, STEP)                                                          \
+  {                                                                                   \
+    const int k_ = min(k_b + 2 * (STEP) + b_half, k_e - 1);                           \
+    _Pragma("unroll") for (int c_ = 0; c_ < 2; ++c_)                                  \
+        rs[SET][c_] = *reinterpret_cast<const v4i*>(bsrc[c_] + size_t(k_) * 1024);    \
+  }
+#define IMC_BSTORE(SET, STEP, ST)                                                     \
+  _Pragma("unroll") for (int c_ = 0; c_ < 2; ++c_) {                                  \
+    v4i v_ = rs[SET][c_];                                                             \
+    if (SPLIT && k_b + 2 * (STEP) + b_half >= k_e) v_ = v4i{0, 0, 0, 0};              \
+    *reinterpret_cast<v4i*>(lds + ((ST) + bdst[c_])) = v_;                            \
+  }
 #define IMC_ALOAD(SEG)                                                                \
   _Pragma("unroll") for (int c_ = 0; c_ < ACH; ++c_)                                  \
       ra[c_] = *reinterpret_cast<const v4i*>(asrc[c_] + size_t(SEG) * kRowLen);
@@ -175,117 +196,134 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
   _Pragma("unroll") for (int c_ = 0; c_ < ACH; ++c_)                                  \
       if (adst[c_] >= 0) *reinterpret_cast<v4i*>(ast + (BUF) * abuf + adst[c_]) = ra[c_];
 
-  // Pipeline: B data for step j is global-loaded NSETS iterations ahead into
-  // register set (j - 2) % NSETS, written to LDS stage j % 3 two iterations
-  // ahead, and its fragments are read one iteration ahead (while the MFMAs
-  // of the current step run).  Stage (k+2)%3 is overwritten at iteration k;
-  // it was last read at iteration k-2.
-  v4i falo[WM], fahi[WM], fblo[WN], fbhi[WN];     // fragments of the current step
-  v4i nalo[WM], nahi[WM], nblo[WN], nbhi[WN];     // fragments of the next step
-#define IMC_FRAGS(ALO, AHI, BLO, BHI, K)                                              \
+  // Pipeline: step j's database bytes are loaded in step j - 4, written to
+  // LDS stage j % 3 in step j - 2 and read in step j (the first 16 entries'
+  // and the query fragments in the step before it).  The stage written in a
+  // step was last read in the step before.
+  v4i al[NX], ah[NX], fbl[2], fbh[2];
+  // byte offset, in the query buffers, of this lane's half of K-step STEP
+  const auto a_step = [&](int step) __attribute__((always_inline)) {
+    const int k0 = min(k_b + 2 * step, k_e - 1), k1 = min(k_b + 2 * step + 1, k_e - 1);
+    const int s0 = k0 / kSegSteps, s1 = k1 / kSegSteps;
+    const uint32_t o0 = (s0 & 1) * abuf + 32 * (k0 - s0 * kSegSteps);
+    const uint32_t o1 = (s1 & 1) * abuf + 32 * (k1 - s1 * kSegSteps);
+    return second ? o1 : o0;
+  };
+#define IMC_AFRAG(X, OFF)                                                             \
   {                                                                                   \
-    const int kk_ = (K);                                                              \
-    const int seg_ = kk_ / kSegSteps, ts_ = kk_ - seg_ * kSegSteps;                   \
-    const int8_t* sb_ = bst + (kk_ % 3) * kBStage;                                    \
-    const int8_t* sa_ = ast + (seg_ & 1) * abuf + 32 * ts_;                           \
-    _Pragma("unroll") for (int x_ = 0; x_ < WM; ++x_) {                               \
-      const int32_t* pa_ = reinterpret_cast<const int32_t*>(sa_ + a_off[x_]);         \
-      const int32_t* ph_ = reinterpret_cast<const int32_t*>(sa_ + a_off[x_] + kSegBytes); \
-      ALO[x_] = v4i{pa_[0], pa_[1], pa_[2], pa_[3]};                                  \
-      AHI[x_] = v4i{ph_[0], ph_[1], ph_[2], ph_[3]};                                  \
-    }                                                                                 \
-    _Pragma("unroll") for (int y_ = 0; y_ < WN; ++y_) {                               \
-      const int8_t* pb_ = sb_ + (wn * WN + y_) * 2048 + lane * 16;                    \
-      BLO[y_] = *reinterpret_cast<const v4i*>(pb_);                                   \
-      BHI[y_] = *reinterpret_cast<const v4i*>(pb_ + 1024);                            \
-    }                                                                                 \
+    const int32_t* pl_ = reinterpret_cast<const int32_t*>(ast + ((OFF) + a_off[X]));  \
+    const int32_t* ph_ = pl_ + kSegBytes / 4;                                         \
+    al[X] = v4i{pl_[0], pl_[1], pl_[2], pl_[3]};                                      \
+    ah[X] = v4i{ph_[0], ph_[1], ph_[2], ph_[3]};                                      \
   }
+#define IMC_BFRAG(Y, ST)                                                              \
+  fbl[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + wn * 8192 + (Y) * 2048 + lane * 16)); \
+  fbh[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + wn * 8192 + (Y) * 2048 + 1024 + lane * 16));
 
-  // prologue: A segment 0; B steps 0 and 1 in stages 0 and 1; steps 2.. in registers
   IMC_ALOAD(seg_b)
   IMC_ASTORE(seg_b & 1)
-  {
-    v4i r0[kBPerThread];
-    IMC_BLOAD(r0, k_b)
-    IMC_BSTORE(r0, k_b % 3)
-    IMC_BLOAD(r0, k_b + 1)
-    IMC_BSTORE(r0, (k_b + 1) % 3)
-  }
-#pragma unroll
-  for (int set = 0; set < NSETS; ++set) { IMC_BLOAD(rs[set], k_b + set + 2) }
+  IMC_BLOAD(0, 0)
+  IMC_BLOAD(1, 1)
+  IMC_BSTORE(0, 0, 0)
+  IMC_BSTORE(1, 1, kRotStage)
+  IMC_BLOAD(0, 2)
+  IMC_BLOAD(1, 3)
   IMC_ALOAD(min(seg_b + 1, seg_e - 1))
   __syncthreads();
   // a wave whose rows are all past the last row (the partial last row tile)
   // only stages operands for the others: no fragment reads, no MFMAs
-  const bool live = m0 + uint32_t(wm * WM * 32) < args.rows;
+  const bool live = m0 + uint32_t(wm * NX * 16) < args.rows;
+  uint32_t st0 = 0, st1 = kRotStage, st2 = 2 * kRotStage;      // stages of steps j, j + 1, j + 2
+  // the next segment's query bytes go to the other A buffer (last read at the
+  // end of the previous segment) in the middle of this one
+#define IMC_TURN(STEP)                                                                \
+  {                                                                                   \
+    const int k_ = k_b + 2 * (STEP), seg_ = k_ / kSegSteps;                           \
+    if (((k_ - seg_ * kSegSteps + 1) >> 1) == 6 && seg_ + 1 < seg_e) {                \
+      IMC_ASTORE((seg_ + 1) & 1)                                                      \
+      IMC_ALOAD(min(seg_ + 2, seg_e - 1))                                             \
+    }                                                                                 \
+    __syncthreads();                                                                  \
+    const uint32_t st_ = st0;                                                         \
+    st0 = st1;                                                                        \
+    st1 = st2;                                                                        \
+    st2 = st_;                                                                        \
+  }
   if (!live) {
-    for (int k0 = k_b; k0 < k_e; k0 += NSETS) {
+    for (int j0 = 0; j0 < steps; j0 += 2) {
 #pragma unroll
-      for (int uu = 0; uu < NSETS; ++uu) {
-        const int k = k0 + uu;
-        const int seg = k / kSegSteps, ts = k - seg * kSegSteps;
-        IMC_BSTORE(rs[uu], (k + 2) % 3)
-        if (ts == kSegSteps / 2 && seg + 1 < seg_e) {
-          IMC_ASTORE((seg + 1) & 1)
-          IMC_ALOAD(min(seg + 2, seg_e - 1))
-        }
-        __syncthreads();
-        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, k_e - 1))
+      for (int uu = 0; uu < 2; ++uu) {
+        IMC_BSTORE(uu, j0 + uu + 2, st2)
+        IMC_BLOAD(uu, j0 + uu + 4)
+        IMC_TURN(j0 + uu)
       }
     }
   } else {
-    IMC_FRAGS(falo, fahi, fblo, fbhi, k_b)
-
-    for (int k0 = k_b; k0 < k_e; k0 += NSETS) {
+    {
+      const uint32_t o = a_step(0);
 #pragma unroll
-      for (int uu = 0; uu < NSETS; ++uu) {
-        const int k = k0 + uu;
-        const int seg = k / kSegSteps, ts = k - seg * kSegSteps;
-        // interleave the next step's fragment reads with this step's MFMAs
-        // (the compiler's single-wave small-GEMM schedule; ~1.5 % faster here)
-        __builtin_amdgcn_iglp_opt(1);
-        IMC_FRAGS(nalo, nahi, nblo, nbhi, min(k + 1, k_e - 1))
+      for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, o) }
+      IMC_BFRAG(0, 0)
+    }
+    for (int j0 = 0; j0 < steps; j0 += 2) {
 #pragma unroll
-        for (int x = 0; x < WM; ++x)
+      for (int uu = 0; uu < 2; ++uu) {
+        const int j = j0 + uu;
+        const uint32_t a_next = a_step(j + 1);
 #pragma unroll
-          for (int y = 0; y < WN; ++y) {
-            acc0[x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(falo[x], fblo[y], acc0[x][y], 0, 0, 0);
-            acc1[x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(falo[x], fbhi[y], acc1[x][y], 0, 0, 0);
-            acc1[x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fahi[x], fblo[y], acc1[x][y], 0, 0, 0);
+        for (int y = 0; y < 4; ++y) {
+          __builtin_amdgcn_sched_barrier(0);
+          IMC_BFRAG((y + 1) & 3, y == 3 ? st1 : st0)
+          v4i cl[NX], ch[NX];
+#pragma unroll
+          for (int x = 0; x < NX; ++x) { cl[x] = al[x]; ch[x] = ah[x]; }
+          if (y == 3) {
+#pragma unroll
+            for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, a_next) }
           }
-        IMC_BSTORE(rs[uu], (k + 2) % 3)             // step k + 2
-        // mid-segment: the next segment's query bytes go to the other A buffer
-        // (last read during the previous segment), then its loads are issued
-        // for the segment after it.
-        if (ts == kSegSteps / 2 && seg + 1 < seg_e) {
-          IMC_ASTORE((seg + 1) & 1)
-          IMC_ALOAD(min(seg + 2, seg_e - 1))
+#pragma unroll
+          for (int x2 = 0; x2 < NX; x2 += 2)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+              // two row blocks together: their high-limb products last
+              const int x = x2 + (i < 4 ? i >> 1 : i & 1);
+              if (x >= NX) continue;
+              if (i >= 4)
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ch[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
+              else if (i & 1)
+                acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cl[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
+              else
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cl[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
+            }
+          if (y == 0) {
+            IMC_BSTORE(uu, j + 2, st2)
+            IMC_BLOAD(uu, j + 4)
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
-        IMC_BLOAD(rs[uu], min(k + 2 + NSETS, k_e - 1))
-#pragma unroll
-        for (int x = 0; x < WM; ++x) { falo[x] = nalo[x]; fahi[x] = nahi[x]; }
-#pragma unroll
-        for (int y = 0; y < WN; ++y) { fblo[y] = nblo[y]; fbhi[y] = nbhi[y]; }
+        IMC_TURN(j)
       }
     }
   }
-#undef IMC_FRAGS
+#undef IMC_TURN
+#undef IMC_AFRAG
+#undef IMC_BFRAG
 #undef IMC_BLOAD
 #undef IMC_BSTORE
 #undef IMC_ALOAD
 #undef IMC_ASTORE
 
+  // 16 x 16 block: lane l holds column l % 16, register e row 4 (l / 16) + e
   uint16_t* out = args.out;
 #pragma unroll
-  for (int x = 0; x < WM; ++x)
+  for (int x = 0; x < NX; ++x)
 #pragma unroll
-    for (int y = 0; y < WN; ++y) {
-      const uint64_t col = uint64_t(t) * kBN + (wn * WN + y) * 32 + (lane & 31);
+    for (int y = 0; y < 4; ++y) {
+      const uint64_t col = uint64_t(t) * kRotN + wn * 64 + y * 16 + (lane & 15);
       if (col >= args.n) continue;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const uint32_t row = m0 + (wm * WM + x) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t row = m0 + (wm * NX + x) * 16 + 4 * (lane >> 4) + e;
         if (row < args.rows) {
           const uint32_t z = uint32_t(acc0[x][y][e]) + (uint32_t(acc1[x][y][e]) << 8);
           if (SPLIT)
@@ -297,32 +335,53 @@ __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, ui
     }
 }
 
+// A last row tile of few rows spreads them over all the waves, 16, 32 or 48
+// each: with 64 a wave, a tile of 31 rows is one live wave pair on two of the
+// four SIMDs.  us, 64 rows a wave / spread, 65,536 entries: 1 query of 31
+// rotations 1,299 / 1,079, 4 of 15: 1,199 / 1,138, 12 of 15: 1,930 / 1,847.
+template <int K, int ACH, bool SPLIT = false>
+__device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, uint32_t t, int vec, int8_t* lds) {
+  const uint32_t rows = args.rows - u * kRotM;
+  if (rows > 192)
+    rot_dot_rows<K, ACH, 4, SPLIT>(args, u, t, vec, lds);
+  else if (rows > 128)
+    rot_dot_rows<K, ACH, 3, SPLIT>(args, u, t, vec, lds);
+  else if (rows > 64)
+    rot_dot_rows<K, ACH, 2, SPLIT>(args, u, t, vec, lds);
+  else
+    rot_dot_rows<K, ACH, 1, SPLIT>(args, u, t, vec, lds);
+}
+
 // One launch per call: workgroup i is output tile (u, t) in an XCD-aware
 // order (consecutive workgroups go to the 8 XCDs in turn; each XCD walks
 // every row tile of its column tiles, so a column tile's database bytes are
 // read into one XCD's L2).
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_kernel(RotDotArgs args) {
+template <int K, int ACH>
+__global__ void __launch_bounds__(kRotThreads) rot_dot_kernel(RotDotArgs args) {
   extern __shared__ __align__(16) int8_t lds[];
   const int vec = blockIdx.z;
   const uint32_t i = blockIdx.x;
-  const uint32_t xcd = i & 7, s8 = i >> 3;
-  const uint32_t u = s8 % args.mt, tg = s8 / args.mt;
-  const uint32_t t = tg * 8 + xcd;
+  const uint32_t first = (args.nt + 7) / 8 * 8 * args.lead;    // workgroups of the leading row tiles
+  uint32_t u = args.lead, t = i - first;
+  if (i < first) {
+    const uint32_t xcd = i & 7, s8 = i >> 3;
+    u = s8 % args.lead;
+    t = s8 / args.lead * 8 + xcd;
+  }
   if (t >= args.nt) return;
   const RotTile tile{args.qop, args.qidx, args.b, args.out[vec], args.rot, args.ld, args.b_block0, args.b_blocks,
                      args.n, args.rows, args.r, args.max_q, 0, 0, nullptr};
-  rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>(tile, u, t, vec, lds);
+  rot_dot_tile<K, ACH>(tile, u, t, vec, lds);
 }
 
 // The same with a tile's segments split over args.splits workgroups, for
 // calls with fewer tiles than CUs: their time is that of one workgroup's
-// serial K loop, 0.26 us a step with one wave row live and 0.47 with all
-// (800 steps), at whatever size.  Each part's sums go to scratch as u32 and
-// reduce_parts_kernel adds them.  31 rows x 1,000 entries: 209 -> 27 us;
-// 1,984 rows x 64 entries: 394 -> 48 us; 93 rows x 4,000: 244 -> 90.
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_split_kernel(RotDotArgs args) {
+// serial K loop, 0.7 us a step with up to 64 rows and 1.3 with all 256 (400
+// steps), at whatever size.  Each part's sums go to scratch as u32 and
+// reduce_parts_kernel adds them.  31 rows x 1,000 entries: 209 -> 25 us;
+// 1,984 rows x 64 entries: 394 -> 43 us; 93 rows x 4,000: 244 -> 90.
+template <int K, int ACH>
+__global__ void __launch_bounds__(kRotThreads) rot_dot_split_kernel(RotDotArgs args) {
   using G = Geo<K>;
   extern __shared__ __align__(16) int8_t lds[];
   const int vec = blockIdx.z;
@@ -332,12 +391,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_split_kernel(R
   const uint32_t u = s8 % args.mt, tp = (s8 / args.mt) * 8 + xcd;
   if (tp >= args.nt * args.splits) return;
   const uint32_t t = tp / args.splits, part = tp % args.splits;
-  constexpr int kSegs = G::kChunks / 2 / (kRowLen / 32);
+  constexpr int kSegs = G::kChunks / 2 / kSegSteps;
   const RotTile tile{args.qop, args.qidx, args.b, nullptr, args.rot, args.ld, args.b_block0, args.b_blocks,
                      args.n, args.rows, args.r, args.max_q, int(part * args.seg_per),
                      min(int((part + 1) * args.seg_per), kSegs),
                      args.part + (uint64_t(vec) * args.splits + part) * args.rows * args.n};
-  rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH, true>(tile, u, t, vec, lds);
+  rot_dot_tile<K, ACH, true>(tile, u, t, vec, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -364,8 +423,8 @@ struct RotGroupsArgs {
   RotGroup g[kMaxDotGroups];
 };
 
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_groups_kernel(RotGroupsArgs args) {
+template <int K, int ACH>
+__global__ void __launch_bounds__(kRotThreads) rot_dot_groups_kernel(RotGroupsArgs args) {
   extern __shared__ __align__(16) int8_t lds[];
   const int vec = blockIdx.z;
   bool first = true;
@@ -384,8 +443,22 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_groups_kernel(
     first = false;
     const RotTile tile{grp.qop, nullptr, args.b, grp.out[vec], grp.rot, args.ld, args.b_block0, args.b_blocks,
                        args.n, grp.rows, grp.r, args.max_q, 0, 0, nullptr};
-    rot_dot_tile<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>(tile, u, t, vec, lds);
+    rot_dot_tile<K, ACH>(tile, u, t, vec, lds);
   }
+}
+
+// Row tiles of a launch that go first: all but a last one of up to 128 rows,
+// whose workgroups are the shorter ones, so that they fill the ends of the CUs'
+// work; in the column tiles' order they would keep the longer tiles of a
+// column apart.  A launch of many rounds has no ends to fill and reads the
+// database once less in one order.  us, in order / apart, 65,536 entries, 15
+// rotations: 18 queries 3,599 / 3,214, 40 5,676 / 5,397, 52 7,247 / 6,920, 70
+// (20 rounds of one tile per CU) 8,987 / 8,798; last tiles of 163 and 192
+// rows no better (5,979 / 6,004, 7,706 / 7,948); 40 queries against 300,000
+// (55 rounds) 24,718 / 24,911, 64 x 17 against 100,000 (31) 13,733 / 13,981.
+uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles) {
+  const uint32_t mt = uint32_t((rows + kRotM - 1) / kRotM);
+  return mt > 1 && rows - uint64_t(mt - 1) * kRotM <= 128 && tiles <= 24 * 256 ? mt - 1 : mt;
 }
 
 // The query slots of a 256-row tile (ceil(256 / r) + 1 of them) must fit the
@@ -766,12 +839,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot_dma_kernel(Rot
     }
 }
 
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
+template <int K, int ACH>
 static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot,
                                  const int8_t* b,
                                  uint64_t first_entry, uint64_t n, uint16_t* code, uint16_t* mask, uint64_t ld,
                                  hipStream_t s, const DotScratch& scratch) {
-  constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N, kThreads = 64 * WAVES_M * WAVES_N;
+  constexpr int kBM = kRotM, kBN = kRotN, kThreads = kRotThreads;
   const uint32_t rows = q * r;
   if (rows == 0 || n == 0) return hipSuccess;
   if (r < 13) return hipErrorInvalidValue;
@@ -796,15 +869,15 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   const uint32_t ntg = (d.nt + 7) / 8;
   if (uint64_t(ntg) * 8 * d.mt > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const dim3 grid(ntg * 8 * d.mt, 1, mask ? 2 : 1);   // z: code, mask
-  const size_t lds = 3 * size_t(kBN / 32) * 2 * 2 * 32 * 16 + 2 * size_t(d.max_q) * 2 * kSegBytes;
+  const size_t lds = 3 * size_t(kRotStage) + 2 * size_t(d.max_q) * 2 * kSegBytes;
   // one workgroup per CU (its LDS): split the segments while CUs are left over
-  constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / (kRowLen / 32);
+  constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / kSegSteps;
   const uint32_t splits = dot_splits(uint64_t(d.mt) * d.nt * grid.z, 1, kSegs, uint64_t(rows) * n * grid.z, scratch);
   if (splits > 1) {
     d.seg_per = (kSegs + splits - 1) / splits;
     d.splits = (kSegs + d.seg_per - 1) / d.seg_per;
     d.part = scratch.part;
-    auto kern = rot_dot_split_kernel<K, WM, WN, WAVES_M, WAVES_N, 5, ACH>;
+    auto kern = rot_dot_split_kernel<K, ACH>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
@@ -816,7 +889,8 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   }
   d.splits = d.seg_per = 0;
   d.part = nullptr;
-  auto kern = rot_dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>;
+  d.lead = rot_lead_tiles(rows, uint64_t(d.mt) * d.nt * grid.z);
+  auto kern = rot_dot_kernel<K, ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
@@ -907,8 +981,7 @@ template <int K, int ACH>
 static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups, const int8_t* b,
                                         uint64_t first_entry, uint64_t n, uint64_t ld, bool persistent,
                                         hipStream_t s) {
-  constexpr int WM = 2, WN = 2, WAVES_M = 4, WAVES_N = 2, NSETS = 4;
-  constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N, kThreads = 64 * WAVES_M * WAVES_N;
+  constexpr int kBM = kRotM, kBN = kRotN, kThreads = kRotThreads;
   RotGroupsArgs d;
   d.b = b;
   d.ld = ld;
@@ -943,8 +1016,8 @@ static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups
   d.ngroups = used;
   d.ntiles = uint32_t(tiles);
   d.max_q = max_q;
-  const size_t lds = 3 * size_t(kBN / 32) * 2 * 2 * 32 * 16 + 2 * size_t(max_q) * 2 * kSegBytes;
-  auto kern = rot_dot_groups_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, ACH>;
+  const size_t lds = 3 * size_t(kRotStage) + 2 * size_t(max_q) * 2 * kSegBytes;
+  auto kern = rot_dot_groups_kernel<K, ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
@@ -981,23 +1054,23 @@ hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const
 }
 
 hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch) {
-  // 0: 8 waves of 64 x 64, loads 6 steps ahead; 2: HBM -> LDS copies, 8
+  // 0: 8 waves of 64 x 64, loads 4 steps of 64 bytes ahead; 2: HBM -> LDS copies, 8
   // stages; 3: database fragments straight into registers
   if (galois) {
     switch (kind) {
       case 2: return launch_rot_dma<kKGalois>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
       case 3: return launch_rot_gb<kKGalois, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
       default:
-        if (c.r >= 22) return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
-        return launch_rot_cfg<kKGalois, 2, 2, 4, 2, 4, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+        if (c.r >= 22) return launch_rot_cfg<kKGalois, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+        return launch_rot_cfg<kKGalois, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
     }
   }
   switch (kind) {
     case 2: return launch_rot_dma<kK>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
     case 3: return launch_rot_gb<kK, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s);
     default:
-      if (c.r >= 22) return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
-      return launch_rot_cfg<kK, 2, 2, 4, 2, 4, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+      if (c.r >= 22) return launch_rot_cfg<kK, 3>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
+      return launch_rot_cfg<kK, 5>(c.qop, c.qidx, c.q, c.r, c.rot, c.b, c.first_entry, c.n, c.code, c.mask, c.ld, s, scratch);
   }
 }
 
