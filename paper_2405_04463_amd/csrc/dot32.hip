@@ -252,16 +252,27 @@ __global__ void __launch_bounds__(256) dot32_kernel(Dot32Args args) {
 
 // ---------------------------------------------------------------------------
 // Rotation-aware dot kernel over Z_2^32 (r >= 13 rotations per query).  A
-// row tile of kBM (query, rotation) rows holds only ceil(kBM / r) + 1
+// row tile of 128 (query, rotation) rows holds only ceil(128 / r) + 1
 // distinct queries, so the workgroup keeps each tile query's bytes of the
 // current 800-byte angular-row segment in LDS (four limb planes, circular
 // padding as in the Z_2^16 kernel) and every lane reads its rotated fragment
-// in place; the database tile streams through three LDS stages, one K-step
-// per stage.  Database data is loaded NSETS steps ahead into registers; the
-// next query segment is loaded during the current one and stored half-way
-// through it into the other of two A buffers.  A wave's tile of WM x WN
-// 32 x 32 blocks needs 64 WM WN accumulator registers (four limb sums), so
-// tiles stay small: two waves per SIMD at 32 x 64.
+// in place; the next segment goes to the other of two buffers during the
+// current one.  The database tile of 128 entries streams through two LDS
+// stages of one K-step each.
+//
+// A K-step is 64 bytes of k, two of the 25 half-steps of a segment (every
+// second segment starts with the second half of a K-step: each lane reads its
+// half's segment), and 10 16 x 16 x 64 MFMAs for each product of 16 rows and
+// 16 entries.  8 waves of 32 x 64: the four limb sums of 32 x 64 take 128
+// accumulator registers.  A last row tile of up to 64 rows gives each wave 16.
+//
+// What bounds it: power, as in rot_dot.hip (a register-only loop of this MFMA
+// on random bytes runs at 4.0 POP/s, of the 32 x 32 x 32 one at 3.35).  us,
+// with 32 x 32 x 32 MFMAs, three stages and 32 rows per wave at any row count
+// / as it stands, 32,768 entries: 32 queries of 31 rotations 6,594 / 5,834
+// (2.85 POP/s), 16 of 15: 1,950 / 1,629, 4 of 31: 1,027 / 901, 1 of 31: 1,065 /
+// 544 (6.2 TB/s).  The limb products in the other order, and no scheduling
+// fences between the 16-entry groups: 1 % slower.
 // ---------------------------------------------------------------------------
 struct RotDot32Args {
   const int8_t* qop;     // [q][limb 4][25600]
@@ -275,192 +286,204 @@ struct RotDot32Args {
   int8_t rot[IMC_MAX_ROT_DEV];
 };
 
-template <int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot32_kernel(RotDot32Args args) {
-  constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N;
-  constexpr int kThreads = 64 * WAVES_M * WAVES_N;
-  constexpr int kBBlk = kBN / 32;
-  constexpr int kBChunks = kBBlk * kLimbs32 * 2 * 32;          // 16-byte chunks per K-step
-  constexpr int kBPerThread = kBChunks / kThreads;
-  constexpr int kBStage = kBChunks * 16;
-  constexpr int kSlotBytes = kLimbs32 * kSegBytes;              // one query's segment, four limbs
-  static_assert(kBChunks % kThreads == 0, "B chunks must divide evenly");
-  extern __shared__ __align__(16) int8_t lds[];
-  int8_t* bst = lds;                                            // 3 B stages
-  int8_t* ast = lds + 3 * kBStage;                              // 2 A segment buffers
-  const uint32_t abuf = args.max_q * kSlotBytes;
+constexpr int kRot32M = 128, kRot32N = 128, kRot32Threads = 512;
+constexpr int kRot32Stage = kRot32N * kLimbs32 * 64;            // one K-step of the database
+constexpr int kSlot32Bytes = kLimbs32 * kSegBytes;              // one query's segment, four limbs
 
+template <int ACH, int NX>
+__device__ __forceinline__ void rot_dot32_rows(const RotDot32Args& args, uint32_t u, uint32_t t, int8_t* lds) {
+  int8_t* ast = lds + 2 * kRot32Stage;                          // 2 A segment buffers
+  const uint32_t abuf = args.max_q * kSlot32Bytes;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const uint32_t i = blockIdx.x, xcd = i & 7, s8 = i >> 3;
-  const uint32_t u = s8 % args.mt, t = (s8 / args.mt) * 8 + xcd;
-  if (t >= args.nt) return;
-
-  const uint32_t m0 = u * kBM;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const uint32_t m0 = u * kRot32M;
   const uint32_t q_lo = m0 / args.r;
-  const uint32_t last_row = min(m0 + kBM, args.rows) - 1;
+  const uint32_t last_row = min(m0 + kRot32M, args.rows) - 1;
   const uint32_t nq = last_row / args.r - q_lo + 1;             // <= max_q
 
   // byte offset of this lane's rotated fragment (limb 0) in an A buffer
-  int a_off[WM];
+  int a_off[NX];
 #pragma unroll
-  for (int x = 0; x < WM; ++x) {
-    const uint32_t row = m0 + (wm * WM + x) * 32 + (lane & 31);
+  for (int x = 0; x < NX; ++x) {
+    const uint32_t row = m0 + (wm * NX + x) * 16 + (lane & 15);
     int slot = 0, sft = 0;
     if (row < args.rows) {
       slot = int(row / args.r - q_lo);
       sft = 4 * args.rot[row % args.r];
     }
-    a_off[x] = slot * kSlotBytes + kSegPad - sft + 16 * (lane >> 5);
+    a_off[x] = slot * kSlot32Bytes + kSegPad - sft + 16 * ((lane >> 4) & 1);
   }
+  const bool second = (lane & 32) != 0;                         // this lane's half of a K-step
 
-  // B chunk c of a stage = (block, limb, k-chunk of the step, slot) at byte 16 c
-  const int8_t* bsrc[kBPerThread];
+  // B staging: a wave copies one limb of one half-step of all four 32-entry
+  // blocks.  Unit j, in stage j % 2, holds what step j reads from LDS: its own
+  // entries except each wave's first 16, and those of step j + 1.
+  const int b_half = wave & 1, b_limb = wave >> 1, b_slot = lane & 31;
+  const uint64_t blk0 = uint64_t(t) * (kRot32N / 32);
+  const int8_t* bbase = args.b + size_t(args.b_block0 + blk0) * kBlock32Bytes + size_t(b_limb) * kPlane32Bytes;
+  uint32_t bsrc[4];
 #pragma unroll
-  for (int j = 0; j < kBPerThread; ++j) {
-    const int c = tid + j * kThreads;
-    const int blk = c >> 8, rem = c & 255;
-    const int limb = rem >> 6, kcl = (rem >> 5) & 1, slot = rem & 31;
-    uint64_t cb = uint64_t(t) * kBBlk + blk;
-    cb = cb < args.b_blocks ? cb : args.b_blocks - 1;
-    bsrc[j] = args.b + size_t(args.b_block0 + cb) * kBlock32Bytes + size_t(limb) * kPlane32Bytes + size_t(kcl) * 512 +
-              slot * 16;
-  }
+  for (int j = 0; j < 4; ++j)
+    bsrc[j] = uint32_t(min(blk0 + j, args.b_blocks - 1) - blk0) * uint32_t(kBlock32Bytes) + uint32_t(lane) * 16;
+  const bool b_lead = b_slot < 16;
+  const uint32_t bdst = uint32_t(((b_slot >> 4) * kLimbs32 + b_limb) * 1024 + (b_half * 2 + (lane >> 5)) * 256 +
+                                 (b_slot & 15) * 16);
   // A chunk c of a segment buffer = (query slot, limb, 16-byte piece)
   const int a_chunks = int(nq) * kLimbs32 * kSegChunks;
-  const int8_t* asrc[ACH];
+  uint32_t asrc[ACH];
   int adst[ACH];
+  const int8_t* abase = args.qop + size_t(q_lo) * kQop32RowBytes;
 #pragma unroll
   for (int j = 0; j < ACH; ++j) {
-    int c = tid + j * kThreads;
+    int c = tid + j * kRot32Threads;
     const bool ok = c < a_chunks;
     c = ok ? c : 0;
     const int qs = c / (kLimbs32 * kSegChunks), rem = c % (kLimbs32 * kSegChunks);
     const int limb = rem / kSegChunks, piece = rem % kSegChunks;
     const int src_off = ((piece * 16 - kSegPad) % kRowLen + kRowLen) % kRowLen;   // circular
-    asrc[j] = args.qop + size_t(q_lo + qs) * kQop32RowBytes + size_t(limb) * kK + src_off;
-    adst[j] = ok ? (qs * kSlotBytes + limb * kSegBytes + piece * 16) : -1;
+    asrc[j] = uint32_t(qs) * uint32_t(kQop32RowBytes) + uint32_t(limb * kK + src_off);
+    adst[j] = ok ? (qs * kSlot32Bytes + limb * kSegBytes + piece * 16) : -1;
   }
 
-  v16i acc[4][WM][WN];
+  v4i acc[4][NX][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int x = 0; x < WM; ++x)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
-      for (int y = 0; y < WN; ++y)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[a][x][y][e] = 0;
+      for (int y = 0; y < 4; ++y) acc[a][x][y] = v4i{0, 0, 0, 0};
 
-  constexpr int kSteps = kChunks / 2;         // 800 steps of 32 k
-  constexpr int kSegSteps = kRowLen / 32;     // 25 per segment
-  constexpr int kSegs = kSteps / kSegSteps;   // 32
-  static_assert(kSteps % NSETS == 0, "the K loop is unrolled by NSETS");
-  v4i rs[NSETS][kBPerThread];
-  v4i ra[ACH];
+  constexpr int kHalves = kChunks / 2;            // 800 half-steps of 32 k
+  constexpr int kSteps = kHalves / 2;
+  constexpr int kSegSteps = kRowLen / 32;         // 25 half-steps per segment
+  constexpr int kSegs = kHalves / kSegSteps;      // 32
+  static_assert(kSteps % 2 == 0, "two K-steps per turn of the loop");
+  v4i rs[4], ra;
 
-#define IMC_BLOAD(R, KS)                                                              \
-  _Pragma("unroll") for (int c_ = 0; c_ < kBPerThread; ++c_)                          \
-      R[c_] = *reinterpret_cast<const v4i*>(bsrc[c_] + size_t(2 * (KS)) * 512);
-#define IMC_BSTORE(R, STAGE)                                                          \
-  _Pragma("unroll") for (int c_ = 0; c_ < kBPerThread; ++c_)                          \
-      *reinterpret_cast<v4i*>(bst + (STAGE) * kBStage + (tid + c_ * kThreads) * 16) = R[c_];
-#define IMC_ALOAD(SEG)                                                                \
-  _Pragma("unroll") for (int c_ = 0; c_ < ACH; ++c_)                                  \
-      ra[c_] = *reinterpret_cast<const v4i*>(asrc[c_] + size_t(SEG) * kRowLen);
-#define IMC_ASTORE(BUF)                                                               \
-  _Pragma("unroll") for (int c_ = 0; c_ < ACH; ++c_)                                  \
-      if (adst[c_] >= 0) *reinterpret_cast<v4i*>(ast + (BUF) * abuf + adst[c_]) = ra[c_];
-#define IMC_AFRAGS(FA, K)                                                             \
+#define IMC_BLOAD(J, UNIT)                                                            \
   {                                                                                   \
-    const int kk_ = (K);                                                              \
-    const int seg_ = kk_ / kSegSteps, ts_ = kk_ - seg_ * kSegSteps;                   \
-    const int8_t* sa_ = ast + (seg_ & 1) * abuf + 32 * ts_;                           \
-    _Pragma("unroll") for (int x_ = 0; x_ < WM; ++x_)                                 \
-    _Pragma("unroll") for (int l_ = 0; l_ < kLimbs32; ++l_) {                         \
-      const int32_t* pa_ = reinterpret_cast<const int32_t*>(sa_ + a_off[x_] + l_ * kSegBytes); \
-      FA[x_][l_] = v4i{pa_[0], pa_[1], pa_[2], pa_[3]};                               \
-    }                                                                                 \
+    const uint32_t o0_ = 1024u * uint32_t(min(2 * (UNIT) + b_half, kHalves - 2 + b_half)); \
+    const uint32_t o1_ = 1024u * uint32_t(min(2 * (UNIT) + 2 + b_half, kHalves - 2 + b_half)); \
+    rs[J] = *reinterpret_cast<const v4i*>(bbase + (bsrc[J] + (((J) & 1) == 0 && b_lead ? o1_ : o0_))); \
   }
-#define IMC_BFRAGS(FB, Y, K)                                                          \
+#define IMC_BSTORE(J, ST) *reinterpret_cast<v4i*>(lds + ((ST) + bdst + 8192 * (J))) = rs[J];
+#define IMC_ALOAD(R, C, SEG) R = *reinterpret_cast<const v4i*>(abase + (asrc[C] + uint32_t(SEG) * kRowLen));
+#define IMC_ASTORE(R, C, BUF) \
+  if (adst[C] >= 0) *reinterpret_cast<v4i*>(ast + (BUF) * abuf + adst[C]) = R;
+  v4i fa[NX][kLimbs32], fb[2][kLimbs32];
+  // byte offset, in the query buffers, of this lane's half of K-step STEP
+  const auto a_step = [&](int step) __attribute__((always_inline)) {
+    const int k0 = min(2 * step, kHalves - 2), k1 = k0 + 1;
+    const int s0 = k0 / kSegSteps, s1 = k1 / kSegSteps;
+    const uint32_t o0 = (s0 & 1) * abuf + 32 * (k0 - s0 * kSegSteps);
+    const uint32_t o1 = (s1 & 1) * abuf + 32 * (k1 - s1 * kSegSteps);
+    return second ? o1 : o0;
+  };
+#define IMC_AFRAG(X, OFF)                                                             \
+  _Pragma("unroll") for (int l_ = 0; l_ < kLimbs32; ++l_) {                           \
+    const int32_t* pa_ = reinterpret_cast<const int32_t*>(ast + ((OFF) + a_off[X]) + l_ * kSegBytes); \
+    fa[X][l_] = v4i{pa_[0], pa_[1], pa_[2], pa_[3]};                                  \
+  }
+#define IMC_BFRAG(Y, ST)                                                              \
   _Pragma("unroll") for (int l_ = 0; l_ < kLimbs32; ++l_)                             \
-    FB[l_] = *reinterpret_cast<const v4i*>(bst + ((K) % 3) * kBStage +                \
-                                           ((wn * WN + (Y)) * kLimbs32 + l_) * 1024 + lane * 16);
+      fb[(Y) & 1][l_] = *reinterpret_cast<const v4i*>(lds + ((ST) + wn * 16384 + (Y) * 4096 + l_ * 1024 + lane * 16));
 
-  // prologue: A segment 0; B steps 0 and 1 in stages 0 and 1; steps 2.. in registers
-  IMC_ALOAD(0)
-  IMC_ASTORE(0)
+  // prologue: query segment 0; database units -1 (its part of step 0, in stage
+  // 1) and 0; unit 1 in registers
   {
-    v4i r0[kBPerThread];
-    IMC_BLOAD(r0, 0)
-    IMC_BSTORE(r0, 0)
-    IMC_BLOAD(r0, 1)
-    IMC_BSTORE(r0, 1)
+    v4i r0[ACH];
+#pragma unroll
+    for (int c = 0; c < ACH; ++c) { IMC_ALOAD(r0[c], c, 0) }
+#pragma unroll
+    for (int c = 0; c < ACH; ++c) { IMC_ASTORE(r0[c], c, 0) }
   }
+  if (b_lead) {
 #pragma unroll
-  for (int set = 0; set < NSETS; ++set) { IMC_BLOAD(rs[set], set + 2) }
-  IMC_ALOAD(1)
-  __syncthreads();
-  // Query fragments are double-buffered (read one step ahead); database
-  // fragments of column block y are re-read for the next step right after
-  // the MFMAs of block y have been issued.
-  v4i fa[WM][kLimbs32], na[WM][kLimbs32], fb[WN][kLimbs32];
-  IMC_AFRAGS(fa, 0)
-#pragma unroll
-  for (int y = 0; y < WN; ++y) { IMC_BFRAGS(fb[y], y, 0) }
-
-  // Stage (k+2)%3 is overwritten at step k: it held step k-1, whose
-  // fragments were read during step k-2 and consumed before the barrier that
-  // ends step k-1.
-  for (int k0 = 0; k0 < kSteps; k0 += NSETS) {
-#pragma unroll
-    for (int uu = 0; uu < NSETS; ++uu) {
-      const int k = k0 + uu;
-      const int seg = k / kSegSteps, ts = k - seg * kSegSteps;
-      const int kn = min(k + 1, kSteps - 1);
-      IMC_AFRAGS(na, kn)
-#pragma unroll
-      for (int y = 0; y < WN; ++y) {
-#pragma unroll
-        for (int x = 0; x < WM; ++x)
-#pragma unroll
-          for (int ia = 0; ia < kLimbs32; ++ia)
-#pragma unroll
-            for (int jb = 0; ia + jb < kLimbs32; ++jb)
-              acc[ia + jb][x][y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[x][ia], fb[y][jb], acc[ia + jb][x][y],
-                                                                         0, 0, 0);
-        IMC_BFRAGS(fb[y], y, kn)
-      }
-      IMC_BSTORE(rs[uu], (k + 2) % 3)
-      if (ts == kSegSteps / 2 && seg + 1 < kSegs) {
-        IMC_ASTORE((seg + 1) & 1)
-        IMC_ALOAD(min(seg + 2, kSegs - 1))
-      }
-      __syncthreads();
-      IMC_BLOAD(rs[uu], min(k + 2 + NSETS, kSteps - 1))
-#pragma unroll
-      for (int x = 0; x < WM; ++x)
-#pragma unroll
-        for (int l = 0; l < kLimbs32; ++l) fa[x][l] = na[x][l];
+    for (int j = 0; j < 4; j += 2) {
+      rs[j] = *reinterpret_cast<const v4i*>(bbase + (bsrc[j] + 1024u * b_half));
+      IMC_BSTORE(j, kRot32Stage)
     }
   }
-#undef IMC_AFRAGS
-#undef IMC_BFRAGS
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { IMC_BLOAD(j, 0) }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { IMC_BSTORE(j, 0) }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { IMC_BLOAD(j, 1) }
+  __syncthreads();
+  // a wave whose rows are all past the last row only stages operands
+  const bool live = m0 + uint32_t(wm * NX * 16) < args.rows;
+  if (live) {
+    const uint32_t o = a_step(0);
+#pragma unroll
+    for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, o) }
+    IMC_BFRAG(0, kRot32Stage)
+  }
+  __syncthreads();
+  for (int k0 = 0; k0 < kSteps; k0 += 2) {
+#pragma unroll
+    for (int uu = 0; uu < 2; ++uu) {
+      const int k = k0 + uu;
+      const uint32_t st_read = uu * kRot32Stage, st_write = kRot32Stage - st_read;
+      if (live) {
+        const uint32_t a_next = a_step(k + 1);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          __builtin_amdgcn_sched_barrier(0);
+          IMC_BFRAG((y + 1) & 3, st_read)
+#pragma unroll
+          for (int x = 0; x < NX; ++x) {
+            // products of limbs (i, j), sums i + j in turn
+            constexpr int kI[10] = {3, 2, 2, 1, 1, 1, 0, 0, 0, 0}, kJ[10] = {0, 0, 1, 0, 2, 1, 3, 1, 2, 0};
+#pragma unroll
+            for (int i = 0; i < 10; ++i)
+              acc[kI[i] + kJ[i]][x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[x][kI[i]], fb[y & 1][kJ[i]],
+                                                                              acc[kI[i] + kJ[i]][x][y], 0, 0, 0);
+            if (y == 3) { IMC_AFRAG(x, a_next) }
+          }
+          IMC_BSTORE(y, st_write)
+          IMC_BLOAD(y, k + 2)
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          IMC_BSTORE(j, st_write)
+          IMC_BLOAD(j, k + 2)
+        }
+      }
+      // the next segment's query bytes go to the other A buffer (last read at
+      // the end of the previous segment), a chunk a K-step, loaded one before
+      const int seg = 2 * k / kSegSteps, m = (2 * k - seg * kSegSteps + 1) >> 1;   // m: 1 .. 12 in every segment
+      if (seg + 1 < kSegs) {
+#pragma unroll
+        for (int c = 0; c <= ACH; ++c)
+          if (m == c + 1) {
+            if (c > 0) { IMC_ASTORE(ra, c - 1, (seg + 1) & 1) }
+            if (c < ACH) { IMC_ALOAD(ra, c, seg + 1) }
+          }
+      }
+      __syncthreads();
+    }
+  }
+#undef IMC_AFRAG
+#undef IMC_BFRAG
 #undef IMC_BLOAD
 #undef IMC_BSTORE
 #undef IMC_ALOAD
 #undef IMC_ASTORE
 
+  // 16 x 16 block: lane l holds column l % 16, register e row 4 (l / 16) + e
 #pragma unroll
-  for (int x = 0; x < WM; ++x)
+  for (int x = 0; x < NX; ++x)
 #pragma unroll
-    for (int y = 0; y < WN; ++y) {
-      const uint64_t col = uint64_t(t) * kBN + (wn * WN + y) * 32 + (lane & 31);
+    for (int y = 0; y < 4; ++y) {
+      const uint64_t col = uint64_t(t) * kRot32N + wn * 64 + y * 16 + (lane & 15);
       if (col >= args.n) continue;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const uint32_t row = m0 + (wm * WM + x) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t row = m0 + (wm * NX + x) * 16 + 4 * (lane >> 4) + e;
         if (row < args.rows) {
           const uint32_t z = uint32_t(acc[0][x][y][e]) + (uint32_t(acc[1][x][y][e]) << 8) +
                              (uint32_t(acc[2][x][y][e]) << 16) + (uint32_t(acc[3][x][y][e]) << 24);
@@ -470,10 +493,22 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) rot_dot32_kernel(RotDo
     }
 }
 
-template <int WM, int WN, int WAVES_M, int WAVES_N, int NSETS, int ACH>
+template <int ACH>
+__global__ void __launch_bounds__(kRot32Threads) rot_dot32_kernel(RotDot32Args args) {
+  extern __shared__ __align__(16) int8_t lds[];
+  const uint32_t i = blockIdx.x, xcd = i & 7, s8 = i >> 3;
+  const uint32_t u = s8 % args.mt, t = (s8 / args.mt) * 8 + xcd;
+  if (t >= args.nt) return;
+  if (args.rows - u * kRot32M > 64)
+    rot_dot32_rows<ACH, 2>(args, u, t, lds);
+  else
+    rot_dot32_rows<ACH, 1>(args, u, t, lds);
+}
+
+template <int ACH>
 static hipError_t launch_rot_dot32(const int8_t* qop, uint32_t q, uint32_t r, const int8_t* rot, const int8_t* b,
                                    uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s) {
-  constexpr int kBM = 32 * WM * WAVES_M, kBN = 32 * WN * WAVES_N, kThreads = 64 * WAVES_M * WAVES_N;
+  constexpr int kBM = kRot32M, kBN = kRot32N, kThreads = kRot32Threads;
   RotDot32Args d;
   d.qop = qop;
   d.b = b;
@@ -492,8 +527,8 @@ static hipError_t launch_rot_dot32(const int8_t* qop, uint32_t q, uint32_t r, co
   for (int i = 0; i < IMC_MAX_ROT_DEV; ++i) d.rot[i] = i < int(r) ? rot[i] : 0;
   const uint64_t groups = uint64_t((d.nt + 7) / 8) * 8 * d.mt;
   if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const size_t lds = 3 * size_t(kBN / 32) * kLimbs32 * 2 * 32 * 16 + 2 * size_t(d.max_q) * kLimbs32 * kSegBytes;
-  auto kern = rot_dot32_kernel<WM, WN, WAVES_M, WAVES_N, NSETS, ACH>;
+  const size_t lds = 2 * size_t(kRot32Stage) + 2 * size_t(d.max_q) * kSlot32Bytes;
+  auto kern = rot_dot32_kernel<ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
@@ -607,8 +642,8 @@ hipError_t launch_dot32(const int8_t* qop, uint32_t q, uint32_t r, const int8_t*
   if (rows == 0 || n == 0) return hipSuccess;
   // rotation-aware tiles of 128 x 128 (8 waves of 32 x 64) when the tile's
   // queries fit the A staging (3 chunks per thread: r >= 26; 5: r >= 13)
-  if (r >= 26) return launch_rot_dot32<1, 2, 4, 2, 2, 3>(qop, q, r, rot, b, first_entry, n, out, ld, s);
-  if (r >= 13) return launch_rot_dot32<1, 2, 4, 2, 2, 5>(qop, q, r, rot, b, first_entry, n, out, ld, s);
+  if (r >= 26) return launch_rot_dot32<3>(qop, q, r, rot, b, first_entry, n, out, ld, s);
+  if (r >= 13) return launch_rot_dot32<5>(qop, q, r, rot, b, first_entry, n, out, ld, s);
   Dot32Args d;
   d.qop = qop;
   d.b = b;
