@@ -409,6 +409,24 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
   // 1,551, 128 rows 2,474 / 1,694; 200 rows 2,448 / 2,901 (two row tiles).
   if (!persistent && rows <= 64) return launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rows, n, s, false, scratch, 4);
   if (!persistent && rows <= 128) return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, false, scratch, 2);
+  // Up to 128 rows past the last whole 256-row tile go in a launch of those
+  // tiles, once there is a tile for every CU (fewer split their loop).  us, one
+  // launch / two: 320 rows x 65,536 entries 4,675 / 3,797, 384 x 30,001 2,321 /
+  // 2,014, 260 x 20,000 1,563 / 1,479.
+  const uint32_t whole = rows / 256 * 256, rest = rows - whole;
+  const uint64_t tiles = (n + 127) / 128 * (rows / 256) * (d.out[1] ? 2 : 1);
+  if (!persistent && whole != 0 && rest != 0 && rest <= 128 && tiles >= 256) {
+    d.rows = whole;
+    const hipError_t e = launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, whole, n, s, false, scratch);
+    if (e != hipSuccess) return e;
+    d.a += size_t(whole / 32) * Geo<K>::kBlockBytes;
+    d.a_blocks -= whole / 32;
+    d.rows = rest;
+    for (uint16_t*& o : d.out)
+      if (o) o += uint64_t(whole) * d.ld;
+    return rest <= 64 ? launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rest, n, s, false, scratch, 4)
+                      : launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rest, n, s, false, scratch, 2);
+  }
   return launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, rows, n, s, persistent, scratch);   // 256 x 128, loads 4 steps ahead
 }
 
