@@ -288,6 +288,172 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
   }
 }
 
+// ---------------------------------------------------------------------------
+// The 256 x 128 tile on 16 x 16 x 64 MFMAs: 8 waves of 64 x 64, a K-step of 64
+// bytes of k per plane (two of the layout's half-steps), staged as 1 KB
+// fragments [16 rows or entries][plane][16-byte piece 4][16] through three LDS
+// stages of 48 KB.
+//
+// What bounds it: power (a register-only loop of this MFMA on random bytes
+// runs at 4.0 POP/s, of the 32 x 32 x 32 one at 3.35).  us against 65,536
+// entries, dot_kernel's 256 x 128 tiles of 32 x 32 x 32 MFMAs / these: 160 rows
+// 2,599 / 2,239, 256 2,644 / 2,290, 512 4,944 / 4,220 (3.06 POP/s), 768 7,340 /
+// 6,245; 270 rows x 5,000 entries 495 / 407.  One register set of loads in
+// flight instead of two: 1 - 2 % slower.
+// ---------------------------------------------------------------------------
+constexpr int kWideStage = (256 + 128) * 128;
+
+template <int K, bool SPLIT = false>
+__global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
+  using G = Geo<K>;
+  extern __shared__ __align__(16) int8_t lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int vec = blockIdx.z;
+  // the order of dot_kernel
+  const uint32_t i = blockIdx.x;
+  const uint32_t xcd = i & 7;
+  const uint32_t ntp = SPLIT ? args.nt * args.splits : args.nt;
+  const uint32_t s_end = ((ntp + 7) / 8) * args.mt;
+  const uint32_t s_step = args.persistent ? (gridDim.x >> 3) : s_end;
+  for (uint32_t s = i >> 3; s < s_end; s += s_step) {
+  const uint32_t u = s % args.mt, tg = s / args.mt;
+  const uint32_t tp = tg * 8 + xcd;
+  if (tp >= ntp) continue;
+  const uint32_t t = SPLIT ? tp / args.splits : tp, part = SPLIT ? tp % args.splits : 0;
+
+  // A wave copies one plane of one half-step of four 32-row blocks and two
+  // 32-entry blocks, a lane a 16-byte piece of each.
+  const int half = wave & 1, plane = (wave >> 1) & 1, slot = lane & 31;
+  const int8_t* src[6];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const int blk = (wave >> 2) + 2 * j;
+    const int8_t* base;
+    if (j < 4) {
+      const uint32_t rb = min(u * 8 + blk, args.a_blocks - 1);
+      base = args.a + size_t(rb) * G::kBlockBytes;
+    } else {
+      const uint64_t cb = min(uint64_t(t) * 4 + (blk - 8), args.b_blocks - 1);
+      base = args.b + size_t(args.b_block0 + cb) * G::kBlockBytes;
+    }
+    src[j] = base + size_t(2 * vec + plane) * G::kPlaneBlockBytes + half * 1024 + lane * 16;
+  }
+  const uint32_t dst = uint32_t(((wave >> 2) * 2 + (slot >> 4)) * 2048 + plane * 1024 +
+                                (half * 2 + (lane >> 5)) * 256 + (slot & 15) * 16);
+
+  v4i acc0[4][4], acc1[4][4];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc0[e >> 2][e & 3] = acc1[e >> 2][e & 3] = v4i{0, 0, 0, 0};
+
+  constexpr int kSteps = G::kChunks / 4;
+  static_assert(kSteps % 2 == 0, "two K-steps per turn of the loop");
+  const int k_b = SPLIT ? int(part * args.steps_per) : 0;
+  const int k_e = SPLIT ? min(k_b + int(args.steps_per), kSteps) : kSteps;
+  v4i rs[2][6];
+#define IMC_GLOAD(SET, C, STEP) \
+  rs[SET][C] = *reinterpret_cast<const v4i*>(src[C] + size_t(min((STEP), k_e - 1)) * 2048);
+#define IMC_LSTORE(SET, C, ST) *reinterpret_cast<v4i*>(lds + ((ST) + dst + (C) * 8192)) = rs[SET][C];
+  v4i al[4], ah[4], fbl[2], fbh[2];
+#define IMC_AFRAG(X, ST)                                                              \
+  al[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * 8192 + (X) * 2048 + lane * 16)); \
+  ah[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * 8192 + (X) * 2048 + 1024 + lane * 16));
+#define IMC_BFRAG(Y, ST)                                                              \
+  fbl[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 32768 + wn * 8192 + (Y) * 2048 + lane * 16)); \
+  fbh[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 32768 + wn * 8192 + (Y) * 2048 + 1024 + lane * 16));
+
+  // Pipeline: step j's bytes are loaded in step j - 4, written to LDS
+  // stage j % 3 in step j - 2 and read in step j, the query fragments and the
+  // first 16 entries' in the step before it.  The stage written in a step was
+  // last read in the step before.
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) { IMC_GLOAD(0, c, k_b + h) }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) { IMC_LSTORE(0, c, h * kWideStage) }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < 6; ++c) { IMC_GLOAD(h, c, k_b + 2 + h) }
+  __syncthreads();
+  uint32_t st0 = 0, st1 = kWideStage, st2 = 2 * kWideStage;      // stages of steps j, j + 1, j + 2
+#pragma unroll
+  for (int x = 0; x < 4; ++x) { IMC_AFRAG(x, 0) }
+  IMC_BFRAG(0, 0)
+  for (int k0 = k_b; k0 < k_e; k0 += 2) {
+#pragma unroll
+    for (int uu = 0; uu < 2; ++uu) {
+      const int k = k0 + uu;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        __builtin_amdgcn_sched_barrier(0);
+        IMC_BFRAG((y + 1) & 3, y == 3 ? st1 : st0)
+#pragma unroll
+        for (int x2 = 0; x2 < 4; x2 += 2) {
+#pragma unroll
+          for (int e = 0; e < 6; ++e) {
+            // two row blocks together: their high-limb products last
+            const int x = x2 + (e < 4 ? e >> 1 : e & 1);
+            if (e >= 4)
+              acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
+            else if (e & 1)
+              acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
+            else
+              acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
+          }
+          if (y == 3) {
+            IMC_AFRAG(x2, st1)
+            IMC_AFRAG(x2 + 1, st1)
+          }
+        }
+        if (y < 3) {
+#pragma unroll
+          for (int c = 2 * y; c < 2 * y + 2; ++c) {
+            IMC_LSTORE(uu, c, st2)
+            IMC_GLOAD(uu, c, k + 4)
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+      const uint32_t st = st0;
+      st0 = st1;
+      st1 = st2;
+      st2 = st;
+    }
+  }
+#undef IMC_GLOAD
+#undef IMC_LSTORE
+#undef IMC_AFRAG
+#undef IMC_BFRAG
+
+  // 16 x 16 block: lane l holds column l % 16, register e row 4 (l / 16) + e
+  uint16_t* out = args.out[vec];
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const uint64_t col = uint64_t(t) * 128 + wn * 64 + y * 16 + (lane & 15);
+      if (col >= args.n) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t row = u * 256 + wm * 64 + x * 16 + 4 * (lane >> 4) + e;
+        if (row < args.rows) {
+          const uint32_t z = uint32_t(acc0[x][y][e]) + (uint32_t(acc1[x][y][e]) << 8);
+          if (SPLIT)
+            args.part[((uint64_t(vec) * args.splits + part) * args.rows + row) * args.n + col] = z;
+          else
+            out[uint64_t(row) * args.ld + col] = uint16_t(z);
+        }
+      }
+    }
+  __syncthreads();   // the next tile's prologue reuses the LDS stages
+  }
+}
+
 hipError_t launch_expand(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot, int8_t* a,
                          uint32_t rows_pad, hipStream_t s, bool galois) {
   Rot rr;
@@ -325,12 +491,13 @@ hipError_t launch_reduce_parts(const uint32_t* part, uint32_t splits, uint64_t r
   return hipGetLastError();
 }
 
-template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS>
-static hipError_t launch_dot_cfg(DotArgs d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
-                                 const DotScratch& scratch, uint32_t per_cu = 1) {
-  using C = DotCfg<WM, WN, WAVES_M, WAVES_N>;
-  d.mt = (rows + C::kBM - 1) / C::kBM;
-  d.nt = uint32_t((n + C::kBN - 1) / C::kBN);
+// One launch of a kernel, whole or split, of bm x bn tiles.
+using DotKernel = void (*)(DotArgs);
+static hipError_t launch_tiles(DotKernel kern, DotKernel split, uint32_t bm, uint32_t bn, uint32_t threads, size_t lds,
+                               uint32_t steps, uint32_t piece, DotArgs d, uint32_t rows, uint64_t n, hipStream_t s,
+                               bool persistent, const DotScratch& scratch, uint32_t per_cu) {
+  d.mt = (rows + bm - 1) / bm;
+  d.nt = uint32_t((n + bn - 1) / bn);
   const uint32_t ntg = (d.nt + 7) / 8;
   if (uint64_t(ntg) * 8 * d.mt > 0x7FFFFFFFull) return hipErrorInvalidValue;
   uint32_t blocks = ntg * 8 * d.mt;
@@ -346,37 +513,50 @@ static hipError_t launch_dot_cfg(DotArgs d, uint32_t rows, uint64_t n, hipStream
     }
   }
   const dim3 grid(blocks, 1, d.out[1] ? 2 : 1);   // z: code, mask (no mask dot when masks are public)
-  const size_t lds = 3 * size_t(C::kStageBytes);
-  // Split the K loop while CUs are left over, in pieces of 10 steps: a call of
-  // few tiles takes as long as one workgroup's 800 steps.  1 row x 100
-  // entries 428 -> 18 us, 33 rows x 5,000 entries 448 -> 139.
-  constexpr uint32_t kPieces = Geo<K>::kChunks / 2 / 10;
-  static_assert(10 % NSETS == 0, "a piece is whole unrolled iterations");
+  // Split the K loop while CUs are left over, in pieces of `piece` steps (whole
+  // turns of the loop): a call of few tiles takes as long as one workgroup's
+  // loop.  1 row x 100 entries 428 -> 18 us, 33 rows x 5,000 entries 448 -> 139.
+  const uint32_t pieces = steps / piece;
   const uint32_t splits =
-      dot_splits(uint64_t(d.mt) * d.nt * grid.z, per_cu, kPieces, uint64_t(rows) * n * grid.z, scratch);
+      dot_splits(uint64_t(d.mt) * d.nt * grid.z, per_cu, pieces, uint64_t(rows) * n * grid.z, scratch);
   if (splits > 1) {
-    d.steps_per = (kPieces + splits - 1) / splits * 10;
-    d.splits = (kPieces * 10 + d.steps_per - 1) / d.steps_per;
+    d.steps_per = (pieces + splits - 1) / splits * piece;
+    d.splits = (steps + d.steps_per - 1) / d.steps_per;
     d.part = scratch.part;
     d.persistent = 0;
-    auto kern = dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, true>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(split),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
     const uint32_t ntp = (d.nt * d.splits + 7) / 8 * 8;
-    hipLaunchKernelGGL(kern, dim3(ntp * d.mt, 1, grid.z), dim3(C::kThreads), lds, s, d);
+    hipLaunchKernelGGL(split, dim3(ntp * d.mt, 1, grid.z), dim3(threads), lds, s, d);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_reduce_parts(d.part, d.splits, rows, n, d.out[0], d.out[1], d.ld, s);
   }
   d.splits = d.steps_per = 0;
   d.part = nullptr;
-  auto kern = dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(C::kThreads), lds, s, d);
+  hipLaunchKernelGGL(kern, grid, dim3(threads), lds, s, d);
   return hipGetLastError();
+}
+
+template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS>
+static hipError_t launch_dot_cfg(const DotArgs& d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
+                                 const DotScratch& scratch, uint32_t per_cu = 1) {
+  using C = DotCfg<WM, WN, WAVES_M, WAVES_N>;
+  static_assert(10 % NSETS == 0, "a piece is whole unrolled iterations");
+  return launch_tiles(dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS>,
+                      dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, true>, C::kBM, C::kBN, C::kThreads,
+                      3 * size_t(C::kStageBytes), Geo<K>::kChunks / 2, 10, d, rows, n, s, persistent, scratch, per_cu);
+}
+
+template <int K>
+static hipError_t launch_dot_wide(const DotArgs& d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
+                                  const DotScratch& scratch) {
+  return launch_tiles(dot_wide_kernel<K>, dot_wide_kernel<K, true>, 256, 128, 512, 3 * size_t(kWideStage),
+                      Geo<K>::kChunks / 4, 10, d, rows, n, s, persistent, scratch, 1);
 }
 
 hipError_t launch_expand_rows(const int8_t* qop, uint32_t q, const imc_row* rows, uint32_t nrows, int8_t* a,
@@ -406,18 +586,18 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
   // Up to 64 rows 64 x 128 tiles (36 KB of LDS, four workgroups a CU), up to
   // 128 rows 128 x 128 tiles (two).  us against 65,536 entries, 256-row /
   // these tiles: 1 row 2,158 / 1,125, 64 rows 2,484 / 1,178, 65 rows 2,190 /
-  // 1,551, 128 rows 2,474 / 1,694; 200 rows 2,448 / 2,901 (two row tiles).
+  // 1,551, 128 rows 2,474 / 1,694; 200 rows 2,193 / 2,901 (two row tiles).
   if (!persistent && rows <= 64) return launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rows, n, s, false, scratch, 4);
   if (!persistent && rows <= 128) return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, false, scratch, 2);
   // Up to 128 rows past the last whole 256-row tile go in a launch of those
   // tiles, once there is a tile for every CU (fewer split their loop).  us, one
-  // launch / two: 320 rows x 65,536 entries 4,675 / 3,797, 384 x 30,001 2,321 /
-  // 2,014, 260 x 20,000 1,563 / 1,479.
+  // launch / two, with 256-row tiles as they were: 320 rows x 65,536 entries
+  // 4,675 / 3,797, 384 x 30,001 2,321 / 2,014, 260 x 20,000 1,563 / 1,479.
   const uint32_t whole = rows / 256 * 256, rest = rows - whole;
   const uint64_t tiles = (n + 127) / 128 * (rows / 256) * (d.out[1] ? 2 : 1);
   if (!persistent && whole != 0 && rest != 0 && rest <= 128 && tiles >= 256) {
     d.rows = whole;
-    const hipError_t e = launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, whole, n, s, false, scratch);
+    const hipError_t e = launch_dot_wide<K>(d, whole, n, s, false, scratch);
     if (e != hipSuccess) return e;
     d.a += size_t(whole / 32) * Geo<K>::kBlockBytes;
     d.a_blocks -= whole / 32;
@@ -427,7 +607,7 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
     return rest <= 64 ? launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rest, n, s, false, scratch, 4)
                       : launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rest, n, s, false, scratch, 2);
   }
-  return launch_dot_cfg<K, 2, 2, 4, 2, 2>(d, rows, n, s, persistent, scratch);   // 256 x 128, loads 4 steps ahead
+  return launch_dot_wide<K>(d, rows, n, s, persistent, scratch);
 }
 
 hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const int8_t* b, uint64_t first_entry,
