@@ -12,10 +12,12 @@ import os
 
 import torch
 
-from . import (DOT_PERSISTENT, DOT_TILES_EXPANDED_128x128, DOT_TILES_EXPANDED_256x128, DOT_TILES_EXPANDED_SHALLOW,
+from . import (DOT_PERSISTENT, DOT_TILES_AUTO, DOT_TILES_EXPANDED_128x128, DOT_TILES_EXPANDED_256x128, DOT_TILES_EXPANDED_SHALLOW,
                DOT_TILES_ROTATION, DOT_TILES_ROTATION_DIRECT, DOT_TILES_ROTATION_LDSCOPY)
 
-CANDIDATES_UNIFORM = [DOT_TILES_ROTATION, DOT_TILES_ROTATION_LDSCOPY, DOT_TILES_ROTATION_DIRECT,
+# AUTO plans each call over the kernels that the other names fix one of (and
+# alone takes consecutive rotations in pairs)
+CANDIDATES_UNIFORM = [DOT_TILES_AUTO, DOT_TILES_ROTATION, DOT_TILES_ROTATION_LDSCOPY, DOT_TILES_ROTATION_DIRECT,
                       DOT_TILES_EXPANDED_256x128, DOT_TILES_EXPANDED_256x128 | DOT_PERSISTENT,
                       DOT_TILES_EXPANDED_128x128, DOT_TILES_EXPANDED_SHALLOW]
 CANDIDATES_ROWS = [DOT_TILES_EXPANDED_256x128, DOT_TILES_EXPANDED_256x128 | DOT_PERSISTENT,
