@@ -65,9 +65,10 @@ typedef int imc_status;
                                             enough tiles, else ROTATION when r >= 13, else
                                             EXPANDED_256x128 */
 #define IMC_DOT_TILES_EXPANDED_256x128 1 /* rotated rows expanded into scratch; 256 x 128 tiles,
-                                            8 waves of 64 x 64, global loads 4 K-steps ahead */
+                                            8 waves of 64 x 64, global loads 4 K-steps of 64
+                                            bytes ahead; smaller tiles for up to 128 rows */
 #define IMC_DOT_TILES_EXPANDED_128x128 2 /* as 1 with 128 x 128 tiles, 4 waves */
-#define IMC_DOT_TILES_EXPANDED_SHALLOW 3 /* as 1 with global loads 3 K-steps ahead */
+#define IMC_DOT_TILES_EXPANDED_SHALLOW 3 /* 256 x 128 tiles, K-steps of 32 bytes loaded 3 ahead */
 #define IMC_DOT_TILES_ROTATION 4         /* 256 x 128 tiles; each tile's queries staged unrotated in
                                             LDS per 800-byte segment, rotations read in place
                                             (used when r >= 13, else as AUTO) */
