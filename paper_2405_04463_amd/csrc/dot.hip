@@ -289,23 +289,25 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
 }
 
 // ---------------------------------------------------------------------------
-// The 256 x 128 tile on 16 x 16 x 64 MFMAs: 8 waves of 64 x 64, a K-step of 64
-// bytes of k per plane (two of the layout's half-steps), staged as 1 KB
-// fragments [16 rows or entries][plane][16-byte piece 4][16] through three LDS
-// stages of 48 KB.
+// Tiles of 64 NX rows x 128 entries on 16 x 16 x 64 MFMAs: 8 waves of 16 NX x
+// 64, a K-step of 64 bytes of k per plane (two of the layout's half-steps),
+// staged as 1 KB fragments [16 rows or entries][plane][16-byte piece 4][16]
+// through three LDS stages of 24 (two workgroups a CU) to 48 KB.
 //
-// What bounds it: power (a register-only loop of this MFMA on random bytes
-// runs at 4.0 POP/s, of the 32 x 32 x 32 one at 3.35).  us against 65,536
-// entries, dot_kernel's 256 x 128 tiles of 32 x 32 x 32 MFMAs / these: 160 rows
-// 2,599 / 2,239, 256 2,644 / 2,290, 512 4,944 / 4,220 (3.06 POP/s), 768 7,340 /
-// 6,245; 270 rows x 5,000 entries 495 / 407.  One register set of loads in
-// flight instead of two: 1 - 2 % slower.
-// ---------------------------------------------------------------------------
-constexpr int kWideStage = (256 + 128) * 128;
+// What bounds it: the database stream up to 64 rows (5.7 - 6.2 TB/s), above
+// power (a register-only loop of this MFMA on random bytes runs at 4.0 POP/s,
+// of the 32 x 32 x 32 one at 3.35).  us against 65,536 entries, dot_kernel's
+// tiles of 32 x 32 x 32 MFMAs (64, 128 and 256 rows) / these: 64 rows 1,175 /
+// 1,172, 65 rows 1,625 / 1,305, 100 1,683 / 1,440, 128 1,720 / 1,507, 192 2,582 / 1,860, 256 2,644
+// / 2,290, 512 4,944 / 4,120 (3.1 POP/s), 768 7,340 / 6,245; 270 rows x 5,000
+// entries 495 / 407.  One register set of loads in flight instead of two: 1 -
+// 2 % slower.
+constexpr int wide_stage(int nx) { return (64 * nx + 128) * 128; }
 
-template <int K, bool SPLIT = false>
-__global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
+template <int K, int NX, bool SPLIT = false>
+__global__ void __launch_bounds__(512, NX == 1 ? 4 : 1) dot_wide_kernel(DotArgs args) {
   using G = Geo<K>;
+  constexpr int kStage = wide_stage(NX), kUnits = 2 + NX;
   extern __shared__ __align__(16) int8_t lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -323,19 +325,19 @@ __global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
   if (tp >= ntp) continue;
   const uint32_t t = SPLIT ? tp / args.splits : tp, part = SPLIT ? tp % args.splits : 0;
 
-  // A wave copies one plane of one half-step of four 32-row blocks and two
+  // A wave copies one plane of one half-step of NX 32-row blocks and two
   // 32-entry blocks, a lane a 16-byte piece of each.
   const int half = wave & 1, plane = (wave >> 1) & 1, slot = lane & 31;
-  const int8_t* src[6];
+  const int8_t* src[kUnits];
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {
+  for (int j = 0; j < kUnits; ++j) {
     const int blk = (wave >> 2) + 2 * j;
     const int8_t* base;
-    if (j < 4) {
-      const uint32_t rb = min(u * 8 + blk, args.a_blocks - 1);
+    if (j < NX) {
+      const uint32_t rb = min(u * (2 * NX) + blk, args.a_blocks - 1);
       base = args.a + size_t(rb) * G::kBlockBytes;
     } else {
-      const uint64_t cb = min(uint64_t(t) * 4 + (blk - 8), args.b_blocks - 1);
+      const uint64_t cb = min(uint64_t(t) * 4 + (blk - 2 * NX), args.b_blocks - 1);
       base = args.b + size_t(args.b_block0 + cb) * G::kBlockBytes;
     }
     src[j] = base + size_t(2 * vec + plane) * G::kPlaneBlockBytes + half * 1024 + lane * 16;
@@ -343,25 +345,25 @@ __global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
   const uint32_t dst = uint32_t(((wave >> 2) * 2 + (slot >> 4)) * 2048 + plane * 1024 +
                                 (half * 2 + (lane >> 5)) * 256 + (slot & 15) * 16);
 
-  v4i acc0[4][4], acc1[4][4];
+  v4i acc0[NX][4], acc1[NX][4];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc0[e >> 2][e & 3] = acc1[e >> 2][e & 3] = v4i{0, 0, 0, 0};
+  for (int e = 0; e < 4 * NX; ++e) acc0[e >> 2][e & 3] = acc1[e >> 2][e & 3] = v4i{0, 0, 0, 0};
 
   constexpr int kSteps = G::kChunks / 4;
   static_assert(kSteps % 2 == 0, "two K-steps per turn of the loop");
   const int k_b = SPLIT ? int(part * args.steps_per) : 0;
   const int k_e = SPLIT ? min(k_b + int(args.steps_per), kSteps) : kSteps;
-  v4i rs[2][6];
+  v4i rs[2][kUnits];
 #define IMC_GLOAD(SET, C, STEP) \
   rs[SET][C] = *reinterpret_cast<const v4i*>(src[C] + size_t(min((STEP), k_e - 1)) * 2048);
 #define IMC_LSTORE(SET, C, ST) *reinterpret_cast<v4i*>(lds + ((ST) + dst + (C) * 8192)) = rs[SET][C];
-  v4i al[4], ah[4], fbl[2], fbh[2];
+  v4i al[NX], ah[NX], fbl[2], fbh[2];
 #define IMC_AFRAG(X, ST)                                                              \
-  al[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * 8192 + (X) * 2048 + lane * 16)); \
-  ah[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * 8192 + (X) * 2048 + 1024 + lane * 16));
+  al[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * (2048 * NX) + (X) * 2048 + lane * 16)); \
+  ah[X] = *reinterpret_cast<const v4i*>(lds + ((ST) + wm * (2048 * NX) + (X) * 2048 + 1024 + lane * 16));
 #define IMC_BFRAG(Y, ST)                                                              \
-  fbl[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 32768 + wn * 8192 + (Y) * 2048 + lane * 16)); \
-  fbh[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 32768 + wn * 8192 + (Y) * 2048 + 1024 + lane * 16));
+  fbl[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 8192 * NX + wn * 8192 + (Y) * 2048 + lane * 16)); \
+  fbh[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + 8192 * NX + wn * 8192 + (Y) * 2048 + 1024 + lane * 16));
 
   // Pipeline: step j's bytes are loaded in step j - 4, written to LDS
   // stage j % 3 in step j - 2 and read in step j, the query fragments and the
@@ -370,59 +372,82 @@ __global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) { IMC_GLOAD(0, c, k_b + h) }
+    for (int c = 0; c < kUnits; ++c) { IMC_GLOAD(0, c, k_b + h) }
 #pragma unroll
-    for (int c = 0; c < 6; ++c) { IMC_LSTORE(0, c, h * kWideStage) }
+    for (int c = 0; c < kUnits; ++c) { IMC_LSTORE(0, c, h * kStage) }
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int c = 0; c < 6; ++c) { IMC_GLOAD(h, c, k_b + 2 + h) }
+    for (int c = 0; c < kUnits; ++c) { IMC_GLOAD(h, c, k_b + 2 + h) }
   __syncthreads();
-  uint32_t st0 = 0, st1 = kWideStage, st2 = 2 * kWideStage;      // stages of steps j, j + 1, j + 2
+  uint32_t st0 = 0, st1 = kStage, st2 = 2 * kStage;      // stages of steps j, j + 1, j + 2
+  // a wave whose rows are all past the last row only stages operands (not in
+  // 256-row tiles, where a second loop costs 2 - 3 %)
+  const bool live = NX == 4 || u * (64 * NX) + wm * (16 * NX) < args.rows;
+  if (!live) {
+    for (int k0 = k_b; k0 < k_e; k0 += 2) {
 #pragma unroll
-  for (int x = 0; x < 4; ++x) { IMC_AFRAG(x, 0) }
-  IMC_BFRAG(0, 0)
-  for (int k0 = k_b; k0 < k_e; k0 += 2) {
+      for (int uu = 0; uu < 2; ++uu) {
 #pragma unroll
-    for (int uu = 0; uu < 2; ++uu) {
-      const int k = k0 + uu;
-#pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        __builtin_amdgcn_sched_barrier(0);
-        IMC_BFRAG((y + 1) & 3, y == 3 ? st1 : st0)
-#pragma unroll
-        for (int x2 = 0; x2 < 4; x2 += 2) {
-#pragma unroll
-          for (int e = 0; e < 6; ++e) {
-            // two row blocks together: their high-limb products last
-            const int x = x2 + (e < 4 ? e >> 1 : e & 1);
-            if (e >= 4)
-              acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
-            else if (e & 1)
-              acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
-            else
-              acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
-          }
-          if (y == 3) {
-            IMC_AFRAG(x2, st1)
-            IMC_AFRAG(x2 + 1, st1)
-          }
+        for (int c = 0; c < kUnits; ++c) {
+          IMC_LSTORE(uu, c, st2)
+          IMC_GLOAD(uu, c, k0 + uu + 4)
         }
-        if (y < 3) {
-#pragma unroll
-          for (int c = 2 * y; c < 2 * y + 2; ++c) {
-            IMC_LSTORE(uu, c, st2)
-            IMC_GLOAD(uu, c, k + 4)
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        const uint32_t st = st0;
+        st0 = st1;
+        st1 = st2;
+        st2 = st;
       }
-      __syncthreads();
-      const uint32_t st = st0;
-      st0 = st1;
-      st1 = st2;
-      st2 = st;
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, 0) }
+    IMC_BFRAG(0, 0)
+    for (int k0 = k_b; k0 < k_e; k0 += 2) {
+#pragma unroll
+      for (int uu = 0; uu < 2; ++uu) {
+        const int k = k0 + uu;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          __builtin_amdgcn_sched_barrier(0);
+          IMC_BFRAG((y + 1) & 3, y == 3 ? st1 : st0)
+#pragma unroll
+          for (int x2 = 0; x2 < NX; x2 += 2) {
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+              // two row blocks together: their high-limb products last
+              const int x = x2 + (e < 4 ? e >> 1 : e & 1);
+              if (x >= NX) continue;
+              if (e >= 4)
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
+              else if (e & 1)
+                acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
+              else
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
+            }
+            if (y == 3) {
+              IMC_AFRAG(x2, st1)
+              if constexpr (NX > 1)
+                if (x2 + 1 < NX) { IMC_AFRAG(x2 + 1, st1) }
+            }
+          }
+          if (y < 3) {
+#pragma unroll
+            for (int c = 2 * y; c < min(2 * y + 2, kUnits); ++c) {
+              IMC_LSTORE(uu, c, st2)
+              IMC_GLOAD(uu, c, k + 4)
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        const uint32_t st = st0;
+        st0 = st1;
+        st1 = st2;
+        st2 = st;
+      }
     }
   }
 #undef IMC_GLOAD
@@ -433,14 +458,14 @@ __global__ void __launch_bounds__(512) dot_wide_kernel(DotArgs args) {
   // 16 x 16 block: lane l holds column l % 16, register e row 4 (l / 16) + e
   uint16_t* out = args.out[vec];
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < NX; ++x)
 #pragma unroll
     for (int y = 0; y < 4; ++y) {
       const uint64_t col = uint64_t(t) * 128 + wn * 64 + y * 16 + (lane & 15);
       if (col >= args.n) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t row = u * 256 + wm * 64 + x * 16 + 4 * (lane >> 4) + e;
+        const uint32_t row = u * (64 * NX) + (wm * NX + x) * 16 + 4 * (lane >> 4) + e;
         if (row < args.rows) {
           const uint32_t z = uint32_t(acc0[x][y][e]) + (uint32_t(acc1[x][y][e]) << 8);
           if (SPLIT)
@@ -552,11 +577,12 @@ static hipError_t launch_dot_cfg(const DotArgs& d, uint32_t rows, uint64_t n, hi
                       3 * size_t(C::kStageBytes), Geo<K>::kChunks / 2, 10, d, rows, n, s, persistent, scratch, per_cu);
 }
 
-template <int K>
+template <int K, int NX>
 static hipError_t launch_dot_wide(const DotArgs& d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
                                   const DotScratch& scratch) {
-  return launch_tiles(dot_wide_kernel<K>, dot_wide_kernel<K, true>, 256, 128, 512, 3 * size_t(kWideStage),
-                      Geo<K>::kChunks / 4, 10, d, rows, n, s, persistent, scratch, 1);
+  return launch_tiles(dot_wide_kernel<K, NX>, dot_wide_kernel<K, NX, true>, 64 * NX, 128, 512,
+                      3 * size_t(wide_stage(NX)), Geo<K>::kChunks / 4, 10, d, rows, n, s, persistent, scratch,
+                      NX == 1 ? 2 : 1);
 }
 
 hipError_t launch_expand_rows(const int8_t* qop, uint32_t q, const imc_row* rows, uint32_t nrows, int8_t* a,
@@ -581,14 +607,14 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
     case 3: return launch_dot_cfg<K, 2, 2, 4, 2, 1>(d, rows, n, s, persistent, scratch);    // 256 x 128, loads 3 steps ahead
     default: break;
   }
-  // Few rows: the database stream bounds the call, and a 256-row tile spends
-  // its steps on empty rows with one workgroup a CU waiting for its loads.
-  // Up to 64 rows 64 x 128 tiles (36 KB of LDS, four workgroups a CU), up to
-  // 128 rows 128 x 128 tiles (two).  us against 65,536 entries, 256-row /
-  // these tiles: 1 row 2,158 / 1,125, 64 rows 2,484 / 1,178, 65 rows 2,190 /
-  // 1,551, 128 rows 2,474 / 1,694; 200 rows 2,193 / 2,901 (two row tiles).
-  if (!persistent && rows <= 64) return launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rows, n, s, false, scratch, 4);
-  if (!persistent && rows <= 128) return launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rows, n, s, false, scratch, 2);
+  // Few rows: the database stream bounds the call, and a tile of more rows
+  // spends its steps on empty ones.  us against 65,536 entries, 256-row / these
+  // tiles: 1 row 2,158 / 1,075, 64 rows 2,484 / 1,172, 65 rows 2,190 / 1,305, 128
+  // rows 2,290 / 1,507, 150 rows 2,140 / 1,860; 200 rows 2,165 (192-row tiles
+  // would be two).
+  if (!persistent && rows <= 64) return launch_dot_wide<K, 1>(d, rows, n, s, false, scratch);
+  if (!persistent && rows <= 128) return launch_dot_wide<K, 2>(d, rows, n, s, false, scratch);
+  if (!persistent && rows <= 192) return launch_dot_wide<K, 3>(d, rows, n, s, false, scratch);
   // Up to 128 rows past the last whole 256-row tile go in a launch of those
   // tiles, once there is a tile for every CU (fewer split their loop).  us, one
   // launch / two, with 256-row tiles as they were: 320 rows x 65,536 entries
@@ -597,17 +623,17 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
   const uint64_t tiles = (n + 127) / 128 * (rows / 256) * (d.out[1] ? 2 : 1);
   if (!persistent && whole != 0 && rest != 0 && rest <= 128 && tiles >= 256) {
     d.rows = whole;
-    const hipError_t e = launch_dot_wide<K>(d, whole, n, s, false, scratch);
+    const hipError_t e = launch_dot_wide<K, 4>(d, whole, n, s, false, scratch);
     if (e != hipSuccess) return e;
     d.a += size_t(whole / 32) * Geo<K>::kBlockBytes;
     d.a_blocks -= whole / 32;
     d.rows = rest;
     for (uint16_t*& o : d.out)
       if (o) o += uint64_t(whole) * d.ld;
-    return rest <= 64 ? launch_dot_cfg<K, 2, 1, 1, 4, 2>(d, rest, n, s, false, scratch, 4)
-                      : launch_dot_cfg<K, 2, 2, 2, 2, 2>(d, rest, n, s, false, scratch, 2);
+    return rest <= 64 ? launch_dot_wide<K, 1>(d, rest, n, s, false, scratch)
+                      : launch_dot_wide<K, 2>(d, rest, n, s, false, scratch);
   }
-  return launch_dot_wide<K>(d, rows, n, s, persistent, scratch);
+  return launch_dot_wide<K, 4>(d, rows, n, s, persistent, scratch);
 }
 
 hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const int8_t* b, uint64_t first_entry,

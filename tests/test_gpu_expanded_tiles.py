@@ -1,4 +1,4 @@
-"""The expanded kernel's 256-row tiles at the edges of their rows, the rows past
+"""The expanded kernel's tiles at the edges of their rows, the rows past
 the last whole tile in a launch of their own (from 256 tiles on) or not,
 against its 128 x 128 tiles."""
 import numpy as np
@@ -24,6 +24,9 @@ def dev64(a):
     (25, 13, 16385, 0, False, True),     # 325: 69, expanded on request
     (64, 6, 16385, 0, True, True),       # 384: 128
     (35, 11, 16385, 0, True, False),     # 385: 129, in the second tile
+    (48, 4, 16385, 0, False, True),      # 192-row tiles, whole
+    (43, 3, 16385, 64, True, True),      # 129 in one: its last wave row idle
+    (19, 5, 16400, 0, True, True),       # 128-row tiles, 95 rows
 ])
 def test_expanded_rows(keys, q, r, n, first, galois, mask):
     if not torch.cuda.is_available():
