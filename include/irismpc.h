@@ -121,7 +121,10 @@ typedef struct imc_ids {
  * 102,400 B per row, 32 MiB for the parts of dot products whose K loop is
  * split, and a few counters) and, the first time on a device,
  * looks up the device address of the static array that
- * imc_dot_shares_rows_noalloc uses.  Errors: IMC_EINVAL (null),
+ * imc_dot_shares_rows_noalloc uses.  The parts' scratch serves the first stream
+ * whose dot call splits its K loop, for the life of the context: calls on other
+ * streams and on the per-thread default stream, and captured calls, run with
+ * the loop whole (the same results, slower when tiles are few).  Errors: IMC_EINVAL (null),
  * IMC_EUNSUPPORTED (code_bits, thr_a, flags; device index >= 64),
  * IMC_ENOMEM, IMC_EDEVICE. */
 imc_status imc_create(const imc_params* params, int device, imc_ctx** out);

@@ -25,8 +25,8 @@ struct imc_ctx {
   size_t rot_op_bytes;
   unsigned long long* bad;        // open-check counter
   imc::DotScratch parts;          // parts of a split dot product's K loop
-  bool parts_owned;               // set by the first call that may split ...
-  hipStream_t parts_stream;       // ... on this stream
+  imc::PartsOwner owner;
+  std::mutex parts_mu;            // held from the check of the owner to the last launch that uses the parts
 };
 
 // 1,984 rows x 64 entries in 16 parts of both vectors take half of it; a call
@@ -93,23 +93,27 @@ imc_status check_ids(const imc_ids* ids) {
   return IMC_OK;
 }
 
-// The parts scratch for a call on `stream`.  One stream owns it, the first one
-// that asks: its calls run in order.  Calls on other streams, and captured
-// ones (a graph may be replayed beside eager calls), do not split.
-imc::DotScratch parts_for(imc_ctx* c, hipStream_t stream) {
-  imc::DotScratch none;
-  none.cus = c->parts.cus;
-  if (c->parts_owned && c->parts_stream != stream) return none;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return none;
+// The parts scratch for a call on `stream`, held while the call is enqueued.
+// Where it is not lent, the call does not split.
+class PartsLease {
+ public:
+  PartsLease(imc_ctx* c, hipStream_t stream) : lock_(c->parts_mu) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(stream, &st) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    scratch = c->parts;
+    if (!c->owner.lends(reinterpret_cast<uintptr_t>(stream), stream == hipStreamPerThread,
+                        !known || st != hipStreamCaptureStatusNone)) {
+      scratch.part = nullptr;
+      scratch.bytes = 0;
+      lock_.unlock();
+    }
   }
-  if (st != hipStreamCaptureStatusNone) return none;
-  c->parts_owned = true;
-  c->parts_stream = stream;
-  return c->parts;
-}
+  imc::DotScratch scratch;
+
+ private:
+  std::unique_lock<std::mutex> lock_;
+};
 
 size_t blocks_for(size_t capacity) { return (capacity + 31) / 32; }
 
@@ -172,10 +176,12 @@ imc_status imc_create(const imc_params* p, int device, imc_ctx** out) {
   }
   c->parts.part = reinterpret_cast<uint32_t*>(c->rot_op + c->rot_op_bytes);
   c->parts.bytes = kPartBytes;
+  c->parts.owner = &c->owner;
   c->bad = reinterpret_cast<unsigned long long*>(c->rot_op + c->rot_op_bytes + kPartBytes);
   imc_status rs = resolve_scratch(device);   // the device is current (guard above)
   if (rs == IMC_OK &&
-      hipDeviceGetAttribute(&c->parts.cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+      (hipDeviceGetAttribute(&c->parts.cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+       hipEventCreateWithFlags(&c->parts.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess))
     rs = IMC_EDEVICE;
   if (rs != IMC_OK) {
     (void)hipFree(c->rot_op);
@@ -190,6 +196,7 @@ void imc_destroy(imc_ctx* c) {
   if (!c) return;
   DeviceGuard g(c->device);
   (void)hipDeviceSynchronize();
+  (void)hipEventDestroy(c->parts.done);
   (void)hipFree(c->rot_op);
   delete c;
 }
@@ -264,10 +271,10 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
     // rotations read straight from the unrotated operand staged in LDS
     const imc::RotCall call{static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
                             static_cast<const int8_t*>(db), ids->first_entry_id, n, code_dot, mask_dot, ld};
-    const imc::DotScratch parts = parts_for(c, hipStream_t(stream));
+    const PartsLease parts(c, hipStream_t(stream));
     return dev_status(tiles == IMC_DOT_TILES_AUTO
-                          ? imc::launch_rotations(call, hipStream_t(stream), galois, parts)
-                          : imc::launch_rot_dot(call, hipStream_t(stream), kind, galois, parts));
+                          ? imc::launch_rotations(call, hipStream_t(stream), galois, parts.scratch)
+                          : imc::launch_rot_dot(call, hipStream_t(stream), kind, galois, parts.scratch));
   }
   const uint32_t rows_pad = uint32_t(blocks_for(rows) * 32);
   hipError_t e = imc::launch_expand(static_cast<const int8_t*>(qop), qidx, uint32_t(q), uint32_t(ids->r), ids->rot,
@@ -275,7 +282,7 @@ imc_status dot_shares_impl(imc_ctx* c, int party, const void* qop, const uint32_
   if (e != hipSuccess) return IMC_EDEVICE;
   e = imc::launch_dot(c->rot_op, uint32_t(rows), rows_pad / 32, static_cast<const int8_t*>(db), ids->first_entry_id,
                       n, code_dot, mask_dot, ld, hipStream_t(stream), v, galois,
-                      parts_for(c, hipStream_t(stream)));
+                      PartsLease(c, hipStream_t(stream)).scratch);
   return dev_status(e);
 }
 
@@ -310,7 +317,7 @@ imc_status dot_shares_rows_impl(imc_ctx* c, int party, const void* qop, size_t q
     v = (v & ~0xF) | IMC_DOT_TILES_EXPANDED_256x128;
   e = imc::launch_dot(a, uint32_t(nrows), rows_pad / 32, static_cast<const int8_t*>(db), first_entry_id, n,
                       code_dot, mask_dot, ld, hipStream_t(stream), v, galois,
-                      parts_for(c, hipStream_t(stream)));
+                      PartsLease(c, hipStream_t(stream)).scratch);
   return dev_status(e);
 }
 

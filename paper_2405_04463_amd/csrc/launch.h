@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/irismpc.h"
+#include "plan.h"
 
 #define IMC_MAX_ROT_DEV IMC_MAX_ROT
 
@@ -31,26 +32,29 @@ hipError_t launch_galois_append(const uint16_t* const raw[3], uint64_t qi, uint8
 
 hipError_t launch_expand(const int8_t* qop, const uint32_t* qidx, uint32_t q, uint32_t r, const int8_t* rot, int8_t* a,
                          uint32_t rows_pad, hipStream_t s, bool galois);
-// Scratch of a dot call: where the parts of a split K loop go (u32 sums), and
-// the CUs of the device.
+// Scratch of a dot call: where the parts of a split K loop go (u32 sums; none
+// if `bytes` is 0), and the CUs of the device.
 struct DotScratch {
   uint32_t* part = nullptr;
   size_t bytes = 0;
   int cus = 0;
+  PartsOwner* owner = nullptr;
+  hipEvent_t done = nullptr;   // recorded by the last launch that used the parts
+  // Before the launches of a split call on s.  A stream's own calls follow one
+  // another and wait for nothing; a new stream under a destroyed one's handle
+  // waits for what that one left running.
+  hipError_t begin(hipStream_t s) const {
+    const hipError_t e = owner->owned ? hipStreamWaitEvent(s, done, 0) : hipSuccess;
+    owner->take(reinterpret_cast<uintptr_t>(s));
+    return e;
+  }
 };
-// Workgroups that share one tile's K loop: as many as find a CU (`per_cu`
-// workgroups each) beside the call's `tiles`, at most `units` of the loop's
-// pieces and what the scratch holds (`outputs` u32 a part).  1: no split.
 inline uint32_t dot_splits(uint64_t tiles, uint32_t per_cu, uint32_t units, uint64_t outputs,
                            const DotScratch& scratch) {
-  if (!scratch.part || tiles == 0 || outputs == 0) return 1;
-  uint64_t s = uint64_t(scratch.cus) * per_cu / tiles;
-  s = s < units ? s : units;
-  const uint64_t fit = scratch.bytes / 4 / outputs;
-  s = s < fit ? s : fit;
-  return s < 1 ? 1 : uint32_t(s);
+  return dot_splits(tiles, per_cu, units, outputs, scratch.bytes, scratch.cus);
 }
-hipError_t launch_reduce_parts(const uint32_t* part, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
+// Adds the parts of a split call and ends its use of the scratch.
+hipError_t launch_reduce_parts(const DotScratch& scratch, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
                                uint16_t* mask, uint64_t ld, hipStream_t s);
 bool rot_dot_applies(uint32_t r, int kind);
 // One dot call at r >= 13 rotations: q queries (rows of qop, or those that

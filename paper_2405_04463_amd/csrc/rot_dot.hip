@@ -880,12 +880,13 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
     auto kern = rot_dot_split_kernel<K, ACH>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e == hipSuccess) e = scratch.begin(s);
     if (e != hipSuccess) return e;
     const uint32_t ntp = (d.nt * d.splits + 7) / 8 * 8;
     hipLaunchKernelGGL(kern, dim3(ntp * d.mt, 1, grid.z), dim3(kThreads), lds, s, d);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce_parts(d.part, d.splits, rows, n, code, mask, ld, s);
+    return launch_reduce_parts(scratch, d.splits, rows, n, code, mask, ld, s);
   }
   d.splits = d.seg_per = 0;
   d.part = nullptr;
