@@ -819,7 +819,8 @@ imc_status imc_or_tree(imc_ctx* c, const uint64_t* const match[3], size_t q, siz
     if (!match[p] || !dup[p] || !aligned(match[p], 8)) return IMC_EINVAL;
   DeviceGuard g(c->device);
   if (!g.ok) return IMC_EDEVICE;
-  return dev_status(imc::launch_or_tree(c->party, match, q, nw, mw_ld, *ids, ws, dup, hipStream_t(stream)));
+  return dev_status(imc::launch_or_tree(c->party, match, q, nw, mw_ld, *ids, ws, dup, hipStream_t(stream),
+                                        c->parts.cus));
 }
 
 imc_status imc_open(imc_ctx* c, int kind, const void* const rep[3], size_t count, void* out, int check,

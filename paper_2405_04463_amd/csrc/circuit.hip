@@ -8,6 +8,8 @@
 // 64w + o.  A replicated boolean sharing is held as its three components
 // (party p's view is components p and p-1).  Gates are evaluated in bit
 // order, so the lane streams through its ChaCha12 tape one block at a time.
+#include <algorithm>
+
 #include "bits.h"
 #include "device.h"
 #include "launch.h"
@@ -616,6 +618,8 @@ __global__ void __launch_bounds__(256) reshare_kernel(ReshareArgs a) {
 constexpr int kOrChunk = 1024;          // words of a subtree, ten levels
 constexpr int kOrLevels = 10;
 constexpr int kOrGates = kOrChunk - 1 + 8 * 8;   // its gates, in whole groups of 8 per level
+constexpr int kOrQueries = 64;          // most queries of a workgroup
+constexpr int kOrFold = 3 * 6;          // keys x in-word levels
 
 struct OrArgs {
   Keys3 keys;
@@ -626,6 +630,8 @@ struct OrArgs {
   uint64_t q, len, nw, mw_ld, chunks;
   uint64_t qid_base;
   int32_t r, level, first, last;
+  int32_t per;               // MANY: queries of a workgroup
+  int32_t cap, words, gates; // LDS: words before the second level's, words, gates per key
 };
 
 // One workgroup reduces one chunk of 1,024 words of a query by ten levels: a
@@ -635,18 +641,24 @@ struct OrArgs {
 // index only, so every ChaCha12 block of the chunk is drawn first, one key's
 // block per thread, and the levels follow in LDS: the tree's depth costs LDS
 // round trips instead of a launch and three serial blocks a level.
-// 64 queries x 31,744 words: 270 us over 16 launches, now 60 in two; one query
-// x 496 words: 102 us over 10, now 10 in one.
+// MANY: several queries of one chunk each, side by side (a query of few words
+// has few blocks to draw, and would leave most of a workgroup idle).
+// 64 queries x 31,744 words: 270 us over 16 launches, now 58 in two; one query
+// x 496 words: 101 us over 10, now 9 in one.
+template <bool MANY>
 __global__ void __launch_bounds__(256) or_chunk_kernel(OrArgs a) {
-  __shared__ uint64_t words[kOrChunk + kOrChunk / 2][3];   // the chunk, then every other level
-  __shared__ uint64_t tape[3][kOrGates];
-  __shared__ uint64_t fold[3][6];
-  const uint64_t qi = blockIdx.x / a.chunks, base = blockIdx.x % a.chunks * kOrChunk;
-  const uint64_t stream = (uint64_t(kDomOr) << 56) | ((a.qid_base + qi) & 0xFFFFFFFFFFFFull);
+  extern __shared__ uint64_t or_lds[];
+  uint64_t(*const words)[3] = reinterpret_cast<uint64_t(*)[3]>(or_lds);   // the chunk, then every other level
+  uint64_t* const tape = or_lds + 3 * a.words;                            // [key][query][group of 8]
+  uint64_t* const fold = tape + 3 * a.gates;                              // [query][key][6]
+  const uint64_t q0 = MANY ? blockIdx.x * uint64_t(a.per) : blockIdx.x / a.chunks;
+  const uint64_t base = MANY ? 0 : blockIdx.x % a.chunks * kOrChunk;
+  const int nq = MANY ? int(min(uint64_t(a.per), a.q - q0)) : 1;
   const int len = int(min(a.len - base, uint64_t(kOrChunk)));
   const int tid = threadIdx.x;
-  for (int i = tid; i < len; i += 256) {
-    const uint64_t w = base + i;
+  for (int i = tid; i < nq * len; i += 256) {
+    const int j = MANY ? i / len : 0;
+    const uint64_t qi = q0 + j, w = base + (i - j * len);
     const uint64_t row = a.first ? w / a.nw : 0, col = w - row * a.nw;
 #pragma unroll
     for (int p = 0; p < 3; ++p)
@@ -663,34 +675,41 @@ __global__ void __launch_bounds__(256) or_chunk_kernel(OrArgs a) {
   };
   int total = 0;
   for (int v = 0, l = len; v < levels; ++v, l = (l + 1) / 2) total += groups_of(l, v);
-  for (int it = tid; it < 3 * total; it += 256) {
-    const int k = it / total, slot = it - k * total;
-    int v = 0, l = len, g = slot;
-    for (int ng; g >= (ng = groups_of(l, v)); ++v, l = (l + 1) / 2) g -= ng;
+  const int per_key = nq * total, blocks = 3 * per_key;
+  for (int it = tid; it < blocks + (a.last ? kOrFold * nq : 0); it += 256) {
+    const bool in_word = it >= blocks;      // one of the six levels that fold the last word
+    const int f = it - blocks;
+    const int k = in_word ? f / 6 % 3 : it / per_key;
+    const int at = in_word ? 0 : it - k * per_key;
+    const int j = !MANY ? 0 : in_word ? f / kOrFold : at / total;
+    int v = in_word ? levels + f % 6 : 0, l = len, g = in_word ? 0 : at - j * total;
+    if (!in_word)
+      for (int ng; g >= (ng = groups_of(l, v)); ++v, l = (l + 1) / 2) g -= ng;
+    const uint64_t stream = (uint64_t(kDomOr) << 56) | ((a.qid_base + q0 + j) & 0xFFFFFFFFFFFFull);
     uint32_t F[16];
-    chacha12(a.keys.k[k], stream, (uint64_t(a.level + v) << 40) + (base >> (v + 4)) + g, F);
+    chacha12(a.keys.k[k], stream, (uint64_t(a.level + v) << 40) + (in_word ? 0 : (base >> (v + 4)) + g), F);
+    if (in_word) {
+      fold[f] = uint64_t(F[0]) | (uint64_t(F[1]) << 32);
+      continue;
+    }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) tape[k][8 * slot + u] = uint64_t(F[2 * u]) | (uint64_t(F[2 * u + 1]) << 32);
-  }
-  if (a.last && tid < 18) {
-    const int k = tid / 6, v = tid % 6;
-    uint32_t F[16];
-    chacha12(a.keys.k[k], stream, uint64_t(a.level + levels + v) << 40, F);
-    fold[k][v] = uint64_t(F[0]) | (uint64_t(F[1]) << 32);
+    for (int u = 0; u < 8; ++u) tape[k * a.gates + 8 * at + u] = uint64_t(F[2 * u]) | (uint64_t(F[2 * u + 1]) << 32);
   }
   __syncthreads();
-  int cur = 0, l = len, groups = 0;   // this level's words start at words[cur]
+  int cur = 0, l = len, groups = 0;   // this level's words start at words[cur], query j's l words at cur + j * l
   for (int v = 0; v < levels; ++v) {
-    const int half = (l + 1) / 2, next = kOrChunk - cur;
-    for (int i = tid; i < half; i += 256) {
-      const int t = 8 * groups + int((base >> (v + 1)) & 7) + i;
+    const int half = (l + 1) / 2, next = a.cap - cur;
+    for (int i = tid; i < nq * half; i += 256) {
+      const int j = MANY ? i / half : 0, g = i - j * half;
+      const uint64_t* t = tape + 8 * (j * total + groups) + int((base >> (v + 1)) & 7) + g;
+      const int at = cur + j * l + 2 * g;
       B3 x, y;
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        x.c[p] = words[cur + 2 * i][p];
-        y.c[p] = 2 * i + 1 < l ? words[cur + 2 * i + 1][p] : 0;
+        x.c[p] = words[at][p];
+        y.c[p] = 2 * g + 1 < l ? words[at + 1][p] : 0;
       }
-      const B3 z = bx(bx(x, y), band(x, y, tape[0][t], tape[1][t], tape[2][t]));
+      const B3 z = bx(bx(x, y), band(x, y, t[0], t[a.gates], t[2 * a.gates]));
 #pragma unroll
       for (int p = 0; p < 3; ++p) words[next + i][p] = z.c[p];
     }
@@ -699,18 +718,20 @@ __global__ void __launch_bounds__(256) or_chunk_kernel(OrArgs a) {
     cur = next;
     __syncthreads();
   }
-  if (tid != 0) return;
-  B3 w{{words[cur][0], words[cur][1], words[cur][2]}};
+  if (tid >= nq) return;
+  B3 w{{words[cur + tid][0], words[cur + tid][1], words[cur + tid][2]}};
   if (!a.last) {
 #pragma unroll
     for (int p = 0; p < 3; ++p) a.out[uint64_t(blockIdx.x) * 3 + p] = w.c[p];
     return;
   }
+  const uint64_t qi = q0 + tid;
+  const uint64_t* const f = fold + kOrFold * tid;
 #pragma unroll
   for (int v = 0; v < 6; ++v) {
     const int sh = 32 >> v;
     const B3 y{{w.c[0] >> sh, w.c[1] >> sh, w.c[2] >> sh}};
-    w = bx(bx(w, y), band(w, y, fold[0][v], fold[1][v], fold[2][v]));
+    w = bx(bx(w, y), band(w, y, f[v], f[6 + v], f[12 + v]));
   }
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
@@ -910,7 +931,7 @@ size_t or_tree_ws_bytes(uint64_t q, uint64_t r, uint64_t nw) {
 }
 
 hipError_t launch_or_tree(const Keys3& keys, const uint64_t* const match[3], uint64_t q, uint64_t nw, uint64_t mw_ld,
-                          const imc_ids_dev& ids, void* ws, uint8_t* const dup[3], hipStream_t s) {
+                          const imc_ids_dev& ids, void* ws, uint8_t* const dup[3], hipStream_t s, int cus) {
   if (q == 0) return hipSuccess;
   uint64_t len = uint64_t(ids.r) * nw;
   // pass i writes q * ceil(len / 1024^i) words: the two halves of ws in turn
@@ -934,8 +955,25 @@ hipError_t launch_or_tree(const Keys3& keys, const uint64_t* const match[3], uin
     a.level = pass * kOrLevels;
     a.first = pass == 0;
     a.last = a.chunks == 1;
-    if (q > 0x7FFFFFFFull / a.chunks) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(or_chunk_kernel, dim3(unsigned(q * a.chunks)), dim3(256), 0, s, a);
+    const int clen = int(std::min<uint64_t>(len, kOrChunk));
+    int groups = 0;      // of a query's tree; of any chunk if there are several
+    for (int l = clen; l > 1; l = (l + 1) / 2) groups += ((l + 1) / 2 + 7) / 8;
+    // Queries of one workgroup: one while all workgroups run at once (a CU holds
+    // 8 by their waves, fewer by their LDS), else as many as bring that about and
+    // 64 KB of LDS hold.  us, a workgroup per query / as it stands: 10,000 queries
+    // of 31 words 124 / 16, 10,000 of one 54 / 9, 100,000 of one 505 / 33.
+    const uint64_t lds_query = 24 * (clen + (clen + 1) / 2) + 3 * 64 * groups + 8 * kOrFold;
+    const uint64_t slots = uint64_t(cus > 0 ? cus : 1) * std::min<uint64_t>(8, (160 << 10) / lds_query);
+    const uint64_t most = std::min<uint64_t>(kOrQueries, (64 << 10) / lds_query);
+    a.per = a.last ? int(std::max<uint64_t>(1, std::min(most, (q + slots - 1) / slots))) : 1;
+    a.cap = a.per * clen;
+    a.words = a.cap + a.per * ((clen + 1) / 2);
+    a.gates = a.last ? 8 * a.per * groups : kOrGates;
+    const size_t lds = 8 * (3 * size_t(a.words) + 3 * size_t(a.gates) + size_t(kOrFold) * a.per);
+    const uint64_t grid = (q + a.per - 1) / a.per;
+    if (grid > 0x7FFFFFFFull / a.chunks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(a.per > 1 ? or_chunk_kernel<true> : or_chunk_kernel<false>, dim3(unsigned(grid * a.chunks)),
+                       dim3(256), lds, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.last) return e;
     len = a.chunks;

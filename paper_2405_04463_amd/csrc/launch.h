@@ -138,7 +138,7 @@ size_t db32_bytes(uint64_t capacity);
 size_t query32_op_bytes(uint64_t q);
 size_t or_tree_ws_bytes(uint64_t q, uint64_t r, uint64_t nw);
 hipError_t launch_or_tree(const Keys3& keys, const uint64_t* const match[3], uint64_t q, uint64_t nw, uint64_t mw_ld,
-                          const imc_ids_dev& ids, void* ws, uint8_t* const dup[3], hipStream_t s);
+                          const imc_ids_dev& ids, void* ws, uint8_t* const dup[3], hipStream_t s, int cus);
 hipError_t launch_mask_in_batch(uint64_t* const match[3], uint64_t q, uint32_t r, uint64_t mw_ld, uint64_t word,
                                 uint64_t group, hipStream_t s);
 hipError_t launch_or_pairs(const Keys3& keys, const uint8_t* const in[3], uint64_t count, uint64_t id,
