@@ -402,7 +402,7 @@ imc_status dot_groups_impl(imc_ctx* c, int party, const imc_dot_group* groups, s
   if (!dg.ok) return IMC_EDEVICE;
   const bool persistent = (c->dot_variant & IMC_DOT_PERSISTENT) != 0;
   return dev_status(imc::launch_rot_dot_groups(g, used, static_cast<const int8_t*>(db), first_entry_id, n, ld,
-                                               persistent, hipStream_t(stream), galois));
+                                               persistent, hipStream_t(stream), galois, c->parts.cus));
 }
 }  // namespace
 

@@ -85,7 +85,7 @@ struct DotGroup {
   uint16_t* mask;
 };
 hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const int8_t* b, uint64_t first_entry,
-                                 uint64_t n, uint64_t ld, bool persistent, hipStream_t s, bool galois);
+                                 uint64_t n, uint64_t ld, bool persistent, hipStream_t s, bool galois, int cus);
 hipError_t launch_expand_rows(const int8_t* qop, uint32_t q, const imc_row* rows, uint32_t nrows, int8_t* a,
                               uint32_t rows_pad, hipStream_t s, bool galois);
 hipError_t launch_dot(const int8_t* a, uint32_t rows, uint32_t a_blocks, const int8_t* b, uint64_t first_entry,

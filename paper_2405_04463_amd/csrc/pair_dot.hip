@@ -517,6 +517,8 @@ static uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, cons
   const uint64_t rows = q * r, mt = (rows + 255) / 256, cols = (n + kPairN - 1) / kPairN * vecs;
   const uint32_t splits = dot_splits(mt * cols, 1, 16, rows * n * vecs, scratch);
   if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / splits + 2;
+  const uint32_t m = rot_tile_rows(rows, cols / vecs, vecs, scratch.cus);
+  if (m < 256) return kLaunchCost + rot_tile_cost(m);
   const auto rounds = [&](uint64_t tiles) { return (tiles + scratch.cus - 1) / scratch.cus; };
   const uint64_t lead = rot_lead_tiles(rows, mt * cols);
   return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +

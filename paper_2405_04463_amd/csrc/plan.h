@@ -37,4 +37,23 @@ inline uint32_t dot_splits(uint64_t tiles, uint32_t per_cu, uint32_t units, uint
   return s < 1 ? 1 : uint32_t(s);
 }
 
+// Row tiles of `m` rows.
+inline uint64_t rot_tiles(uint64_t rows, uint64_t m) { return (rows + m - 1) / m; }
+
+// Whether every one of `mt` row tiles' workgroups finds a CU at once, of `nt`
+// column tiles over `vecs` vectors: a column tile's workgroups run on one of the
+// 8 XCDs.
+inline bool one_round(uint64_t mt, uint64_t nt, uint32_t vecs, int cus) {
+  return cus >= 8 && mt * ((nt + 7) / 8) * vecs <= uint64_t(cus) / 8;
+}
+
+// Rows of a tile (64 .. 256) of a rotation call whose loop is not split: the
+// fewest that still leave a CU for every tile.  Such a call takes as long as one
+// tile, and a tile of 64 rows takes half of a whole one's time.
+inline uint32_t rot_tile_rows(uint64_t rows, uint64_t nt, uint32_t vecs, int cus) {
+  for (uint32_t m = 64; m < 256; m += 64)
+    if (one_round(rot_tiles(rows, m), nt, vecs, cus)) return m;
+  return 256;
+}
+
 }  // namespace imc

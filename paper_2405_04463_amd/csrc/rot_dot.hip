@@ -32,7 +32,11 @@ namespace imc {
 // 1.52 / 1.42, 8: 2.32 / 2.11, 16 of 15: 2.39 / 2.18, 40 of 15: 5.95 / 5.39,
 // 64 of 15: 8.16 / 7.71, 64 of 24: 12.2 / 11.1.  Scheduling groups that spread
 // the LDS reads over the MFMAs, and slot strides that keep two queries' rows
-// in different banks, change nothing.
+// in different banks, change nothing.  The next step's query fragments are read
+// under the last two of its four groups of MFMAs: all of them under the last
+// one left a launch of one tile per CU waiting at the barrier (19 queries of
+// 13 rotations x 64 entries, 256-row tiles: 409 us, then 391; 40 queries of 15
+// x 65,536, on one box: 5.48 ms, then 5.34).
 // ---------------------------------------------------------------------------
 struct RotDotArgs {
   const int8_t* qop;     // unrotated query operand, row-major [q][plane 4][K]
@@ -44,6 +48,7 @@ struct RotDotArgs {
   uint64_t b_block0, b_blocks, n;
   uint32_t mt, nt;
   uint32_t lead;         // row tiles that share their column tiles' order; the last one follows if it is not of them
+  uint32_t tile_m;       // rows of a tile: kRotM, fewer where a launch has few tiles
   uint32_t max_q;        // query slots per tile (LDS sizing)
   uint32_t splits, seg_per;   // split launches: workgroups per tile, segments of each
   uint32_t* part;        // split launches: u32 [vec][split][rows][n]
@@ -85,7 +90,7 @@ struct RotTile {
   uint16_t* out;
   const int8_t* rot;
   uint64_t ld, b_block0, b_blocks, n;
-  uint32_t rows, r, max_q;
+  uint32_t rows, r, max_q, tile_m;
   int seg_begin, seg_end;      // SPLIT: the tile's share of the angular-row segments
   uint32_t* part;              // SPLIT: where its sums go, u32 [rows][n]
 };
@@ -116,9 +121,9 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  const uint32_t m0 = u * kRotM;
+  const uint32_t m0 = u * args.tile_m;
   const uint32_t q_lo = m0 / args.r;
-  const uint32_t last_row = min(m0 + kRotM, args.rows) - 1;
+  const uint32_t last_row = min(m0 + args.tile_m, args.rows) - 1;
   const uint32_t nq = last_row / args.r - q_lo + 1;            // <= max_q
 
   const int seg_b = SPLIT ? args.seg_begin : 0, seg_e = SPLIT ? args.seg_end : kHalves / kSegSteps;
@@ -209,12 +214,12 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
     const uint32_t o1 = (s1 & 1) * abuf + 32 * (k1 - s1 * kSegSteps);
     return second ? o1 : o0;
   };
-#define IMC_AFRAG(X, OFF)                                                             \
+#define IMC_AFRAG(LO, HI, X, OFF)                                                     \
   {                                                                                   \
     const int32_t* pl_ = reinterpret_cast<const int32_t*>(ast + ((OFF) + a_off[X]));  \
     const int32_t* ph_ = pl_ + kSegBytes / 4;                                         \
-    al[X] = v4i{pl_[0], pl_[1], pl_[2], pl_[3]};                                      \
-    ah[X] = v4i{ph_[0], ph_[1], ph_[2], ph_[3]};                                      \
+    LO[X] = v4i{pl_[0], pl_[1], pl_[2], pl_[3]};                                      \
+    HI[X] = v4i{ph_[0], ph_[1], ph_[2], ph_[3]};                                      \
   }
 #define IMC_BFRAG(Y, ST)                                                              \
   fbl[(Y) & 1] = *reinterpret_cast<const v4i*>(lds + ((ST) + wn * 8192 + (Y) * 2048 + lane * 16)); \
@@ -262,7 +267,7 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
     {
       const uint32_t o = a_step(0);
 #pragma unroll
-      for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, o) }
+      for (int x = 0; x < NX; ++x) { IMC_AFRAG(al, ah, x, o) }
       IMC_BFRAG(0, 0)
     }
     for (int j0 = 0; j0 < steps; j0 += 2) {
@@ -270,16 +275,14 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
       for (int uu = 0; uu < 2; ++uu) {
         const int j = j0 + uu;
         const uint32_t a_next = a_step(j + 1);
+        v4i nl[NX], nh[NX];
 #pragma unroll
         for (int y = 0; y < 4; ++y) {
           __builtin_amdgcn_sched_barrier(0);
           IMC_BFRAG((y + 1) & 3, y == 3 ? st1 : st0)
-          v4i cl[NX], ch[NX];
+          if (y >= 2) {
 #pragma unroll
-          for (int x = 0; x < NX; ++x) { cl[x] = al[x]; ch[x] = ah[x]; }
-          if (y == 3) {
-#pragma unroll
-            for (int x = 0; x < NX; ++x) { IMC_AFRAG(x, a_next) }
+            for (int x = (y - 2) * NX / 2; x < (y - 1) * NX / 2; ++x) { IMC_AFRAG(nl, nh, x, a_next) }
           }
 #pragma unroll
           for (int x2 = 0; x2 < NX; x2 += 2)
@@ -289,11 +292,11 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
               const int x = x2 + (i < 4 ? i >> 1 : i & 1);
               if (x >= NX) continue;
               if (i >= 4)
-                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ch[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[x], fbl[y & 1], acc1[x][y], 0, 0, 0);
               else if (i & 1)
-                acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cl[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
+                acc0[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbl[y & 1], acc0[x][y], 0, 0, 0);
               else
-                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cl[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
+                acc1[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[x], fbh[y & 1], acc1[x][y], 0, 0, 0);
             }
           if (y == 0) {
             IMC_BSTORE(uu, j + 2, st2)
@@ -301,6 +304,8 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
           }
           __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int x = 0; x < NX; ++x) { al[x] = nl[x]; ah[x] = nh[x]; }
         IMC_TURN(j)
       }
     }
@@ -339,9 +344,15 @@ __device__ __forceinline__ void rot_dot_rows(const RotTile& args, uint32_t u, ui
 // each: with 64 a wave, a tile of 31 rows is one live wave pair on two of the
 // four SIMDs.  us, 64 rows a wave / spread, 65,536 entries: 1 query of 31
 // rotations 1,299 / 1,079, 4 of 15: 1,199 / 1,138, 12 of 15: 1,930 / 1,847.
+// Where a launch has fewer tiles than CUs (rot_tile_rows), its tiles are of 64,
+// 128 or 192 rows: a call whose loop is not split (captured, another
+// stream, groups) takes as long as one tile.  us, 256-row tiles / these: 64
+// queries of 31 x 64 entries 385 / 258, 19 of 13 x 64: 408 / 200, 8 of 31 x 2,000:
+// 384 / 195, 12 of 15 x 8,000: 333 / 306; groups of 20 queries of 13 and 3 of 22
+// x 5,000 entries 439 / 328.
 template <int K, int ACH, bool SPLIT = false>
 __device__ __forceinline__ void rot_dot_tile(const RotTile& args, uint32_t u, uint32_t t, int vec, int8_t* lds) {
-  const uint32_t rows = args.rows - u * kRotM;
+  const uint32_t rows = min(args.rows - u * args.tile_m, args.tile_m);
   if (rows > 192)
     rot_dot_rows<K, ACH, 4, SPLIT>(args, u, t, vec, lds);
   else if (rows > 128)
@@ -370,7 +381,7 @@ __global__ void __launch_bounds__(kRotThreads) rot_dot_kernel(RotDotArgs args) {
   }
   if (t >= args.nt) return;
   const RotTile tile{args.qop, args.qidx, args.b, args.out[vec], args.rot, args.ld, args.b_block0, args.b_blocks,
-                     args.n, args.rows, args.r, args.max_q, 0, 0, nullptr};
+                     args.n, args.rows, args.r, args.max_q, args.tile_m, 0, 0, nullptr};
   rot_dot_tile<K, ACH>(tile, u, t, vec, lds);
 }
 
@@ -393,7 +404,7 @@ __global__ void __launch_bounds__(kRotThreads) rot_dot_split_kernel(RotDotArgs a
   const uint32_t t = tp / args.splits, part = tp % args.splits;
   constexpr int kSegs = G::kChunks / 2 / kSegSteps;
   const RotTile tile{args.qop, args.qidx, args.b, nullptr, args.rot, args.ld, args.b_block0, args.b_blocks,
-                     args.n, args.rows, args.r, args.max_q, int(part * args.seg_per),
+                     args.n, args.rows, args.r, args.max_q, args.tile_m, int(part * args.seg_per),
                      min(int((part + 1) * args.seg_per), kSegs),
                      args.part + (uint64_t(vec) * args.splits + part) * args.rows * args.n};
   rot_dot_tile<K, ACH, true>(tile, u, t, vec, lds);
@@ -419,7 +430,7 @@ struct RotGroup {
 struct RotGroupsArgs {
   const int8_t* b;
   uint64_t ld, b_block0, b_blocks, n;
-  uint32_t nt, ntiles, ngroups, max_q;
+  uint32_t nt, ntiles, ngroups, max_q, tile_m;
   RotGroup g[kMaxDotGroups];
 };
 
@@ -442,7 +453,7 @@ __global__ void __launch_bounds__(kRotThreads) rot_dot_groups_kernel(RotGroupsAr
     if (!first) __syncthreads();
     first = false;
     const RotTile tile{grp.qop, nullptr, args.b, grp.out[vec], grp.rot, args.ld, args.b_block0, args.b_blocks,
-                       args.n, grp.rows, grp.r, args.max_q, 0, 0, nullptr};
+                       args.n, grp.rows, grp.r, args.max_q, args.tile_m, 0, 0, nullptr};
     rot_dot_tile<K, ACH>(tile, u, t, vec, lds);
   }
 }
@@ -861,18 +872,20 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   d.b_block0 = first_entry / 32;
   d.b_blocks = (n + 31) / 32;
   d.n = n;
-  d.mt = (rows + kBM - 1) / kBM;
   d.nt = uint32_t((n + kBN - 1) / kBN);
-  d.max_q = (kBM + r - 1) / r + 1;
+  // one workgroup per CU (its LDS): split the segments while CUs are left over
+  constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / kSegSteps;
+  const uint64_t cols = uint64_t(d.nt) * (mask ? 2 : 1);
+  const uint32_t splits = dot_splits((rows + kBM - 1) / kBM * cols, 1, kSegs, rows * n * (mask ? 2 : 1), scratch);
+  d.tile_m = splits > 1 ? kBM : rot_tile_rows(rows, d.nt, mask ? 2 : 1, scratch.cus);
+  d.mt = (rows + d.tile_m - 1) / d.tile_m;
+  d.max_q = (d.tile_m + r - 1) / r + 1;
   if (int(d.max_q) * 2 * kSegChunks > ACH * kThreads) return hipErrorInvalidValue;
   for (int i = 0; i < IMC_MAX_ROT_DEV; ++i) d.rot[i] = i < int(r) ? rot[i] : 0;
   const uint32_t ntg = (d.nt + 7) / 8;
   if (uint64_t(ntg) * 8 * d.mt > 0x7FFFFFFFull) return hipErrorInvalidValue;
   const dim3 grid(ntg * 8 * d.mt, 1, mask ? 2 : 1);   // z: code, mask
   const size_t lds = 3 * size_t(kRotStage) + 2 * size_t(d.max_q) * 2 * kSegBytes;
-  // one workgroup per CU (its LDS): split the segments while CUs are left over
-  constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / kSegSteps;
-  const uint32_t splits = dot_splits(uint64_t(d.mt) * d.nt * grid.z, 1, kSegs, uint64_t(rows) * n * grid.z, scratch);
   if (splits > 1) {
     d.seg_per = (kSegs + splits - 1) / splits;
     d.splits = (kSegs + d.seg_per - 1) / d.seg_per;
@@ -890,7 +903,7 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   }
   d.splits = d.seg_per = 0;
   d.part = nullptr;
-  d.lead = rot_lead_tiles(rows, uint64_t(d.mt) * d.nt * grid.z);
+  d.lead = d.tile_m < kRotM ? d.mt : rot_lead_tiles(rows, d.mt * cols);
   auto kern = rot_dot_kernel<K, ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
@@ -981,8 +994,8 @@ static hipError_t launch_rot_gb(const int8_t* qop, const uint32_t* qidx, uint32_
 template <int K, int ACH>
 static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups, const int8_t* b,
                                         uint64_t first_entry, uint64_t n, uint64_t ld, bool persistent,
-                                        hipStream_t s) {
-  constexpr int kBM = kRotM, kBN = kRotN, kThreads = kRotThreads;
+                                        hipStream_t s, int cus) {
+  constexpr int kBN = kRotN, kThreads = kRotThreads;
   RotGroupsArgs d;
   d.b = b;
   d.ld = ld;
@@ -991,6 +1004,16 @@ static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups
   d.n = n;
   d.nt = uint32_t((n + kBN - 1) / kBN);
   const uint64_t ntg = (d.nt + 7) / 8;
+  d.tile_m = 64;
+  for (; d.tile_m < kRotM; d.tile_m += 64) {   // as rot_tile_rows, over all groups
+    uint64_t all = 0;
+    uint32_t vecs = 1;
+    for (uint32_t gi = 0; gi < ngroups; ++gi) {
+      all += rot_tiles(uint64_t(groups[gi].q) * groups[gi].r, d.tile_m);
+      if (groups[gi].mask) vecs = 2;
+    }
+    if (one_round(all, d.nt, vecs, cus)) break;
+  }
   uint64_t tiles = 0;
   uint32_t max_q = 0, used = 0;
   bool mask = false;
@@ -1005,10 +1028,10 @@ static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups
     mask = g.mask != nullptr;
     o.rows = rows;
     o.r = g.r;
-    o.mt = (rows + kBM - 1) / kBM;
+    o.mt = (rows + d.tile_m - 1) / d.tile_m;
     o.tile0 = uint32_t(tiles);
     for (int j = 0; j < IMC_MAX_ROT_DEV; ++j) o.rot[j] = j < int(g.r) ? g.rot[j] : 0;
-    max_q = std::max(max_q, (kBM + g.r - 1) / g.r + 1);
+    max_q = std::max(max_q, (d.tile_m + g.r - 1) / g.r + 1);
     tiles += ntg * 8 * o.mt;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
   }
@@ -1026,10 +1049,6 @@ static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups
   if (persistent) {
     // one workgroup per CU (the LDS of a tile allows no second one), a
     // multiple of the 8 XCDs
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      return hipErrorInvalidValue;
     const uint32_t g8 = (uint32_t(cus) + 7) / 8 * 8;
     grid = std::min<uint32_t>(grid, g8);
   }
@@ -1038,8 +1057,8 @@ static hipError_t launch_rot_groups_cfg(const DotGroup* groups, uint32_t ngroups
 }
 
 hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const int8_t* b, uint64_t first_entry,
-                                 uint64_t n, uint64_t ld, bool persistent, hipStream_t s, bool galois) {
-  if (ngroups > uint32_t(kMaxDotGroups)) return hipErrorInvalidValue;
+                                 uint64_t n, uint64_t ld, bool persistent, hipStream_t s, bool galois, int cus) {
+  if (cus <= 0 || ngroups > uint32_t(kMaxDotGroups)) return hipErrorInvalidValue;
   uint32_t rmin = 32;
   for (uint32_t gi = 0; gi < ngroups; ++gi) {
     if (groups[gi].q == 0) continue;
@@ -1048,10 +1067,10 @@ hipError_t launch_rot_dot_groups(const DotGroup* groups, uint32_t ngroups, const
   }
   // the staging of the fewest rotations (the most query slots) sizes the launch
   if (galois)
-    return rmin >= 22 ? launch_rot_groups_cfg<kKGalois, 3>(groups, ngroups, b, first_entry, n, ld, persistent, s)
-                      : launch_rot_groups_cfg<kKGalois, 5>(groups, ngroups, b, first_entry, n, ld, persistent, s);
-  return rmin >= 22 ? launch_rot_groups_cfg<kK, 3>(groups, ngroups, b, first_entry, n, ld, persistent, s)
-                    : launch_rot_groups_cfg<kK, 5>(groups, ngroups, b, first_entry, n, ld, persistent, s);
+    return rmin >= 22 ? launch_rot_groups_cfg<kKGalois, 3>(groups, ngroups, b, first_entry, n, ld, persistent, s, cus)
+                      : launch_rot_groups_cfg<kKGalois, 5>(groups, ngroups, b, first_entry, n, ld, persistent, s, cus);
+  return rmin >= 22 ? launch_rot_groups_cfg<kK, 3>(groups, ngroups, b, first_entry, n, ld, persistent, s, cus)
+                    : launch_rot_groups_cfg<kK, 5>(groups, ngroups, b, first_entry, n, ld, persistent, s, cus);
 }
 
 hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch) {

@@ -18,6 +18,7 @@ int lends(int owned, uintptr_t stream, uintptr_t to, int per_thread, int capturi
 unsigned splits(uint64_t tiles, unsigned per_cu, unsigned units, uint64_t outputs, size_t bytes, int cus) {
   return imc::dot_splits(tiles, per_cu, units, outputs, bytes, cus);
 }
+unsigned tile_rows(uint64_t rows, uint64_t nt, unsigned vecs, int cus) { return imc::rot_tile_rows(rows, nt, vecs, cus); }
 }
 """
 
@@ -52,3 +53,15 @@ def test_splits_stay_within_the_loop_the_cus_and_the_scratch(plan):
     assert f(200, 1, 32, 1000, 1 << 25, 256) == 1
     assert f(2, 1, 32, 1000, 0, 256) == 1                # not lent
     assert f(2, 1, 32, 1 << 40, 1 << 25, 256) == 1
+
+
+def test_rows_of_a_rotation_tile(plan):
+    """The fewest rows at which all tiles run at once, a column tile's on one of 8 XCDs."""
+    f = lambda rows, nt, vecs, cus=256: plan.tile_rows(ctypes.c_uint64(rows), ctypes.c_uint64(nt), vecs, cus)  # noqa: E731
+    assert f(31, 8, 2) == 64 and f(247, 1, 2) == 64
+    assert f(1024, 1, 2) == 64 and f(1025, 1, 2) == 128   # 32 CUs of one XCD: 16 tiles a vector
+    assert f(1025, 1, 1) == 64 and f(2049, 8, 1) == 128
+    assert f(2080, 8, 2) == 192 and f(2080, 9, 2) == 256
+    assert f(104, 40, 1) == 64 and f(260, 40, 2) == 128
+    assert f(200, 129, 2) == 256 and f(128, 65, 2) == 128 and f(128, 129, 2) == 256
+    assert f(31, 8, 2, 8) == 256 and f(31, 8, 2, 16) == 64 and f(31, 8, 2, 0) == 256
