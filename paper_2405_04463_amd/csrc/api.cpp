@@ -785,7 +785,7 @@ imc_status imc_dot32_shares(imc_ctx* c, int party, const void* qop, size_t q, co
   if (!g.ok) return IMC_EDEVICE;
   return dev_status(imc::launch_dot32(static_cast<const int8_t*>(qop), uint32_t(q), uint32_t(ids->r), ids->rot,
                                       static_cast<const int8_t*>(db), ids->first_entry_id, n, dot, ld,
-                                      hipStream_t(stream)));
+                                      hipStream_t(stream), c->parts.cus));
 }
 
 imc_status imc_reshare32(imc_ctx* c, int vec, const uint32_t* const add[3], size_t rows, size_t n, size_t ld,

@@ -9,6 +9,8 @@
 //   acc_s = sum over i + j = s of sum_k a_i b_j      (s = 0..3, 10 products)
 // and z = acc0 + 2^8 acc1 + 2^16 acc2 + 2^24 acc3.  |acc3| <= 4 * 25600 *
 // 2^14 < 2^31, so no accumulator wraps.  One vector (code or mask) per region.
+#include <algorithm>
+
 #include "device.h"
 #include "launch.h"
 
@@ -282,6 +284,7 @@ struct RotDot32Args {
   uint32_t rows, q, r;
   uint64_t b_block0, b_blocks, n;
   uint32_t mt, nt;
+  uint32_t tile_m;       // rows of a tile: kRot32M, 64 where a launch has few tiles
   uint32_t max_q;        // query slots per tile (LDS sizing)
   int8_t rot[IMC_MAX_ROT_DEV];
 };
@@ -297,9 +300,9 @@ __device__ __forceinline__ void rot_dot32_rows(const RotDot32Args& args, uint32_
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const uint32_t m0 = u * kRot32M;
+  const uint32_t m0 = u * args.tile_m;
   const uint32_t q_lo = m0 / args.r;
-  const uint32_t last_row = min(m0 + kRot32M, args.rows) - 1;
+  const uint32_t last_row = min(m0 + args.tile_m, args.rows) - 1;
   const uint32_t nq = last_row / args.r - q_lo + 1;             // <= max_q
 
   // byte offset of this lane's rotated fragment (limb 0) in an A buffer
@@ -499,7 +502,7 @@ __global__ void __launch_bounds__(kRot32Threads) rot_dot32_kernel(RotDot32Args a
   const uint32_t i = blockIdx.x, xcd = i & 7, s8 = i >> 3;
   const uint32_t u = s8 % args.mt, t = (s8 / args.mt) * 8 + xcd;
   if (t >= args.nt) return;
-  if (args.rows - u * kRot32M > 64)
+  if (min(args.rows - u * args.tile_m, args.tile_m) > 64)
     rot_dot32_rows<ACH, 2>(args, u, t, lds);
   else
     rot_dot32_rows<ACH, 1>(args, u, t, lds);
@@ -507,7 +510,8 @@ __global__ void __launch_bounds__(kRot32Threads) rot_dot32_kernel(RotDot32Args a
 
 template <int ACH>
 static hipError_t launch_rot_dot32(const int8_t* qop, uint32_t q, uint32_t r, const int8_t* rot, const int8_t* b,
-                                   uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s) {
+                                   uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s,
+                                   int cus) {
   constexpr int kBM = kRot32M, kBN = kRot32N, kThreads = kRot32Threads;
   RotDot32Args d;
   d.qop = qop;
@@ -520,9 +524,12 @@ static hipError_t launch_rot_dot32(const int8_t* qop, uint32_t q, uint32_t r, co
   d.b_block0 = first_entry / 32;
   d.b_blocks = (n + 31) / 32;
   d.n = n;
-  d.mt = (d.rows + kBM - 1) / kBM;
   d.nt = uint32_t((n + kBN - 1) / kBN);
-  d.max_q = (kBM + r - 1) / r + 1;
+  // us, 128-row tiles / 64 where those all run at once: 8 queries of 13 rotations x
+  // 5,000 entries 697 / 437, 64 of 31 x 64: 653 / 415, 16 of 15 x 1,000: 650 / 403
+  d.tile_m = std::min<uint32_t>(kBM, rot_tile_rows(d.rows, d.nt, 1, cus));
+  d.mt = (d.rows + d.tile_m - 1) / d.tile_m;
+  d.max_q = (d.tile_m + r - 1) / r + 1;
   if (int(d.max_q) * kLimbs32 * kSegChunks > ACH * kThreads) return hipErrorInvalidValue;
   for (int i = 0; i < IMC_MAX_ROT_DEV; ++i) d.rot[i] = i < int(r) ? rot[i] : 0;
   const uint64_t groups = uint64_t((d.nt + 7) / 8) * 8 * d.mt;
@@ -637,13 +644,13 @@ hipError_t launch_share32_query(const Key& dk, int vec, const uint64_t* codes, c
 }
 
 hipError_t launch_dot32(const int8_t* qop, uint32_t q, uint32_t r, const int8_t* rot, const int8_t* b,
-                        uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s) {
+                        uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s, int cus) {
   const uint32_t rows = q * r;
   if (rows == 0 || n == 0) return hipSuccess;
   // rotation-aware tiles of 128 x 128 (8 waves of 32 x 64) when the tile's
   // queries fit the A staging (3 chunks per thread: r >= 26; 5: r >= 13)
-  if (r >= 26) return launch_rot_dot32<3>(qop, q, r, rot, b, first_entry, n, out, ld, s);
-  if (r >= 13) return launch_rot_dot32<5>(qop, q, r, rot, b, first_entry, n, out, ld, s);
+  if (r >= 26) return launch_rot_dot32<3>(qop, q, r, rot, b, first_entry, n, out, ld, s, cus);
+  if (r >= 13) return launch_rot_dot32<5>(qop, q, r, rot, b, first_entry, n, out, ld, s, cus);
   Dot32Args d;
   d.qop = qop;
   d.b = b;

@@ -130,7 +130,7 @@ hipError_t launch_share32_db(const Key& dk, int vec, const uint64_t* codes, cons
 hipError_t launch_share32_query(const Key& dk, int vec, const uint64_t* codes, const uint64_t* masks, uint64_t q,
                                 uint64_t qid_base, int8_t* const op[3], hipStream_t s);
 hipError_t launch_dot32(const int8_t* qop, uint32_t q, uint32_t r, const int8_t* rot, const int8_t* b,
-                        uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s);
+                        uint64_t first_entry, uint64_t n, uint32_t* out, uint64_t ld, hipStream_t s, int cus);
 hipError_t launch_reshare32(const Keys3& keys, int vec, const uint32_t* const add[3], uint64_t rows, uint64_t n,
                             uint64_t ld, const imc_ids_dev& ids, uint32_t* const msg[3], uint32_t* const rep[3],
                             hipStream_t s);
