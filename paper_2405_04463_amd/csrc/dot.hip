@@ -629,7 +629,7 @@ static hipError_t launch_dot_k(DotArgs d, uint32_t rows, uint64_t n, hipStream_t
   // 4,675 / 3,797, 384 x 30,001 2,321 / 2,014, 260 x 20,000 1,563 / 1,479.
   const uint32_t whole = rows / 256 * 256, rest = rows - whole;
   const uint64_t tiles = (n + 127) / 128 * (rows / 256) * (d.out[1] ? 2 : 1);
-  if (!persistent && whole != 0 && rest != 0 && rest <= 128 && tiles >= 256) {
+  if (!persistent && whole != 0 && rest != 0 && rest <= 128 && tiles >= uint64_t(scratch.cus)) {
     d.rows = whole;
     const hipError_t e = launch_dot_wide<K, 4>(d, whole, n, s, false, scratch);
     if (e != hipSuccess) return e;

@@ -53,6 +53,9 @@ inline uint32_t dot_splits(uint64_t tiles, uint32_t per_cu, uint32_t units, uint
                            const DotScratch& scratch) {
   return dot_splits(tiles, per_cu, units, outputs, scratch.bytes, scratch.cus);
 }
+inline DotRoom dot_room(const DotScratch& scratch, bool galois) {
+  return DotRoom{scratch.bytes, scratch.cus, rot_segs(galois)};
+}
 // Adds the parts of a split call and ends its use of the scratch.
 hipError_t launch_reduce_parts(const DotScratch& scratch, uint32_t splits, uint64_t rows, uint64_t n, uint16_t* code,
                                uint16_t* mask, uint64_t ld, hipStream_t s);
@@ -71,9 +74,6 @@ struct RotCall {
   uint64_t ld;
 };
 hipError_t launch_rot_dot(const RotCall& c, hipStream_t s, int kind, bool galois, const DotScratch& scratch);
-// Row tiles of such a launch that are walked column tile by column tile; a
-// last one that is not of them follows.
-uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles);
 // The same with the kernel, or the kernels, chosen for the call's sizes.
 hipError_t launch_rotations(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch);
 // One query group of a fused rotation-aware launch (imc_dot_shares_groups).

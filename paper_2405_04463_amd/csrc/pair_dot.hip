@@ -491,97 +491,6 @@ static hipError_t launch_pair(const RotCall& c, hipStream_t s, bool galois) {
   return galois ? launch_pair_k<kKGalois>(d, c.mask != nullptr, s) : launch_pair_k<kK>(d, c.mask != nullptr, s);
 }
 
-// ---------------------------------------------------------------------------
-// Which kernel takes what of a call at r >= 13 rotations.  Times are counted
-// in units of 5 us of the replicated form.  A call takes its tiles in rounds
-// of one per CU; a tile's time, from 65,536 entries (ms / rounds): rot_dot.hip
-// 2 queries 1.14 / 4, 4: 1.42 / 4, 6: 1.75 / 4, 8: 2.11 / 4 (one row tile), 16:
-// 3.90 / 8, 32: 7.45 / 16, 64: 14.5 / 32; pairs 8 queries 2.65 / 4, 10: 3.06 /
-// 4, 12: 3.06 / 4, 16: 3.39 / 4 (one query tile), 32: 5.86 / 8, 64: 10.9 / 16.
-// The last round is rarely full, and up to 8 queries past a multiple of 16
-// leave half of a pairs' tile idle: those columns and those queries may go to
-// rot_dot.hip's kernel in calls of their own, which splits its loop when its
-// tiles are few.  us, one launch / as planned: 16 queries x 20,011 entries
-// 1,370 / 1,097, 18 x 65,536 5,420 / 4,490, 7 queries x 15 rotations x 20,000
-// 585 / 480.
-// ---------------------------------------------------------------------------
-constexpr uint64_t kLaunchCost = 2;
-
-// A rot_dot.hip tile alone in its columns, and beside others.
-static uint64_t rot_tile_cost(uint64_t rows) { return rows <= 64 ? 56 : rows <= 128 ? 68 : rows <= 192 ? 86 : 105; }
-constexpr uint64_t kRotSharedCost = 94;
-static uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 142 : q > 12 ? 168 : q > 8 ? 153 : 132; }
-
-static uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
-  if (q == 0 || n == 0) return 0;
-  const uint64_t rows = q * r, mt = (rows + 255) / 256, cols = (n + kPairN - 1) / kPairN * vecs;
-  const uint32_t splits = dot_splits(mt * cols, 1, 16, rows * n * vecs, scratch);
-  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / splits + 2;
-  const uint32_t m = rot_tile_rows(rows, cols / vecs, vecs, scratch.cus);
-  if (m < 256) return kLaunchCost + rot_tile_cost(m);
-  const auto rounds = [&](uint64_t tiles) { return (tiles + scratch.cus - 1) / scratch.cus; };
-  const uint64_t lead = rot_lead_tiles(rows, mt * cols);
-  return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +
-         (lead < mt ? rot_tile_cost(rows - lead * 256) * rounds(cols) : 0);
-}
-
-// Column tiles that fill whole rounds, `per` tiles each.
-static uint64_t full_cols(uint64_t n, uint64_t per, const DotScratch& scratch) {
-  return scratch.cus > 0 ? (n + kPairN - 1) / kPairN * per / scratch.cus * scratch.cus / per : 0;
-}
-
-// rot_dot.hip's columns that go in a first call, the whole rounds; all n of
-// them if the last round is better not taken apart.
-static uint64_t rot_first_cols(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
-  const uint64_t m = full_cols(n, (q * r + 255) / 256 * vecs, scratch) * kPairN;
-  if (m == 0 || m >= n) return n;
-  return rot_cost(q, r, m, vecs, scratch) + rot_cost(q, r, n - m, vecs, scratch) < rot_cost(q, r, n, vecs, scratch)
-             ? m
-             : n;
-}
-
-static uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotScratch& scratch) {
-  if (q == 0 || n == 0) return 0;
-  const uint64_t m = rot_first_cols(q, r, n, vecs, scratch);
-  return rot_cost(q, r, m, vecs, scratch) + rot_cost(q, r, n - m, vecs, scratch);
-}
-
-struct RotPlan {
-  uint32_t q;   // queries and columns of the pairs; the rest is rot_dot.hip's
-  uint64_t n;
-};
-
-static RotPlan rot_plan(const RotCall& c, const DotScratch& scratch) {
-  const RotPlan none{0, 0};
-  if (c.r < 27 || c.r > 31 || scratch.cus <= 0) return none;
-  for (uint32_t i = 1; i < c.r; ++i)
-    if (c.rot[i] != c.rot[0] + int(i)) return none;   // consecutive, ascending
-  const uint32_t vecs = c.mask ? 2 : 1;
-  RotPlan best = none;
-  uint64_t least = rot_rounds_cost(c.q, c.r, c.n, vecs, scratch);
-  const uint32_t over = c.q % kPairQ;
-  for (int less = 0; less < 2; ++less) {
-    if (less && (over == 0 || over > kPairQ / 2)) break;
-    const uint32_t q = less ? c.q - over : c.q;
-    if (q == 0) break;
-    const uint64_t per = uint64_t(q + kPairQ - 1) / kPairQ * vecs, nt = (c.n + kPairN - 1) / kPairN;
-    const uint64_t full = full_cols(c.n, per, scratch);
-    for (int part = 0; part < 2; ++part) {
-      const uint64_t cols = part ? full : nt;
-      if (cols == 0 || (part && cols == nt)) break;
-      const uint64_t n = cols * kPairN < c.n ? cols * kPairN : c.n;
-      const uint64_t cost = kLaunchCost + pair_tile_cost(q) * ((cols * per + scratch.cus - 1) / scratch.cus) +
-                            rot_rounds_cost(q, c.r, c.n - n, vecs, scratch) +
-                            rot_rounds_cost(c.q - q, c.r, c.n, vecs, scratch);
-      if (cost < least) {
-        least = cost;
-        best = RotPlan{q, n};
-      }
-    }
-  }
-  return best;
-}
-
 // The call's columns from `from` on.
 static RotCall columns_from(RotCall c, uint64_t from) {
   c.first_entry += from;
@@ -593,14 +502,14 @@ static RotCall columns_from(RotCall c, uint64_t from) {
 
 static hipError_t launch_rot_rounds(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch) {
   RotCall first = c;
-  first.n = scratch.cus > 0 ? rot_first_cols(c.q, c.r, c.n, c.mask ? 2 : 1, scratch) : c.n;
+  first.n = rot_first_cols(c.q, c.r, c.n, c.mask ? 2 : 1, dot_room(scratch, galois));
   const hipError_t e = launch_rot_dot(first, s, 0, galois, scratch);
   return e != hipSuccess || first.n == c.n ? e : launch_rot_dot(columns_from(c, first.n), s, 0, galois, scratch);
 }
 
 hipError_t launch_rotations(const RotCall& c, hipStream_t s, bool galois, const DotScratch& scratch) {
   if (c.q == 0 || c.n == 0) return hipSuccess;
-  const RotPlan p = rot_plan(c, scratch);
+  const RotPlan p = rot_plan(c.q, c.r, c.rot, c.n, c.mask ? 2 : 1, dot_room(scratch, galois));
   if (p.n == 0) return launch_rot_rounds(c, s, galois, scratch);
   RotCall main = c;
   main.q = p.q;

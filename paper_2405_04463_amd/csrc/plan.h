@@ -1,5 +1,6 @@
 // plan.h -- host-side rules of the dot calls that need no GPU: who may use a
-// context's scratch, and how a K loop is split.
+// context's scratch, how a K loop is split, and which kernel takes what of a
+// rotation call.
 #pragma once
 
 #include <stddef.h>
@@ -54,6 +55,136 @@ inline uint32_t rot_tile_rows(uint64_t rows, uint64_t nt, uint32_t vecs, int cus
   for (uint32_t m = 64; m < 256; m += 64)
     if (one_round(rot_tiles(rows, m), nt, vecs, cus)) return m;
   return 256;
+}
+
+// What a call may use: scratch for the parts of its loops, CUs, and the angular
+// segments of its K loop.
+struct DotRoom {
+  size_t bytes;
+  int cus;
+  uint32_t segs;
+};
+constexpr uint32_t rot_segs(bool galois) { return galois ? 16 : 32; }
+
+// Workgroups that share one tile's segments in a rotation call, one per CU (its
+// LDS).  The launch rounds a workgroup's segments up.
+inline uint32_t rot_splits(uint64_t rows, uint64_t n, uint32_t vecs, const DotRoom& room) {
+  const uint64_t tiles = rot_tiles(rows, 256) * ((n + 127) / 128) * vecs;
+  return dot_splits(tiles, 1, room.segs, rows * n * vecs, room.bytes, room.cus);
+}
+
+// Row tiles of a launch that go first: all but a last one of up to 128 rows,
+// whose workgroups are the shorter ones, so that they fill the ends of the CUs'
+// work; in the column tiles' order they would keep the longer tiles of a
+// column apart.  A launch of many rounds has no ends to fill and reads the
+// database once less in one order.  us, in order / apart, 65,536 entries, 15
+// rotations: 18 queries 3,599 / 3,214, 40 5,676 / 5,397, 52 7,247 / 6,920, 70
+// (20 rounds of one tile per CU) 8,987 / 8,798; last tiles of 163 and 192
+// rows no better (5,979 / 6,004, 7,706 / 7,948); 40 queries against 300,000
+// (55 rounds) 24,718 / 24,911, 64 x 17 against 100,000 (31) 13,733 / 13,981.
+inline uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles, int cus) {
+  const uint32_t mt = uint32_t(rot_tiles(rows, 256));
+  return mt > 1 && rows - uint64_t(mt - 1) * 256 <= 128 && tiles <= 24 * uint64_t(cus) ? mt - 1 : mt;
+}
+
+// ---------------------------------------------------------------------------
+// Which kernel takes what of a call at r >= 13 rotations.  Times are counted
+// in units of 5 us of the replicated form.  A call takes its tiles in rounds
+// of one per CU; a tile's time, from 65,536 entries (ms / rounds): rot_dot.hip
+// 2 queries 1.14 / 4, 4: 1.42 / 4, 6: 1.75 / 4, 8: 2.11 / 4 (one row tile), 16:
+// 3.90 / 8, 32: 7.45 / 16, 64: 14.5 / 32; pairs 8 queries 2.65 / 4, 10: 3.06 /
+// 4, 12: 3.06 / 4, 16: 3.39 / 4 (one query tile), 32: 5.86 / 8, 64: 10.9 / 16.
+// The last round is rarely full, and up to 8 queries past a multiple of 16
+// leave half of a pairs' tile idle: those columns and those queries may go to
+// rot_dot.hip's kernel in calls of their own, which splits its loop when its
+// tiles are few.  us, one launch / as planned: 16 queries x 20,011 entries
+// 1,370 / 1,097, 18 x 65,536 5,420 / 4,490, 7 queries x 15 rotations x 20,000
+// 585 / 480.
+// ---------------------------------------------------------------------------
+constexpr uint64_t kLaunchCost = 2;
+constexpr uint32_t kRotCols = 128, kPairQueries = 16;   // entries of a column tile, queries of a pairs' tile
+
+// A rot_dot.hip tile alone in its columns, and beside others.
+inline uint64_t rot_tile_cost(uint64_t rows) { return rows <= 64 ? 56 : rows <= 128 ? 68 : rows <= 192 ? 86 : 105; }
+constexpr uint64_t kRotSharedCost = 94;
+inline uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 142 : q > 12 ? 168 : q > 8 ? 153 : 132; }
+
+// More parts than these, in replicated calls of up to 8 tiles, save up to 3 of
+// a call's units, which is less than the model is true to: counted, they change
+// the route of 4 in 200,000 random calls, to 1.03, 1.04, 0.64 and 0.66 of the
+// speed.
+constexpr uint32_t kPlanSplits = 16;
+
+inline uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
+  if (q == 0 || n == 0) return 0;
+  const uint64_t rows = q * r, nt = (n + kRotCols - 1) / kRotCols, mt = rot_tiles(rows, 256), cols = nt * vecs;
+  const uint32_t splits = rot_splits(rows, n, vecs, room);
+  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / (splits < kPlanSplits ? splits : kPlanSplits) + 2;
+  const uint32_t m = rot_tile_rows(rows, nt, vecs, room.cus);
+  if (m < 256) return kLaunchCost + rot_tile_cost(m);
+  const auto rounds = [&](uint64_t tiles) { return (tiles + room.cus - 1) / room.cus; };
+  const uint64_t lead = rot_lead_tiles(rows, mt * cols, room.cus);
+  return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +
+         (lead < mt ? rot_tile_cost(rows - lead * 256) * rounds(cols) : 0);
+}
+
+// Column tiles that fill whole rounds, `per` tiles each.
+inline uint64_t full_cols(uint64_t n, uint64_t per, const DotRoom& room) {
+  return (n + kRotCols - 1) / kRotCols * per / room.cus * room.cus / per;
+}
+
+// rot_dot.hip's columns that go in a first call, the whole rounds; all n of
+// them if the last round is better not taken apart.
+inline uint64_t rot_first_cols(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
+  if (room.cus <= 0) return n;
+  const uint64_t m = full_cols(n, rot_tiles(q * r, 256) * vecs, room) * kRotCols;
+  if (m == 0 || m >= n) return n;
+  return rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room) < rot_cost(q, r, n, vecs, room)
+             ? m
+             : n;
+}
+
+inline uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
+  if (q == 0 || n == 0) return 0;
+  const uint64_t m = rot_first_cols(q, r, n, vecs, room);
+  return rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room);
+}
+
+struct RotPlan {
+  uint32_t q;   // queries and columns of the pairs; the rest is rot_dot.hip's
+  uint64_t n;
+};
+
+// Pairs take lists of 27 .. 31 consecutive rotations, ascending.
+inline RotPlan rot_plan(uint32_t q_all, uint32_t r, const int8_t* rot, uint64_t n_all, uint32_t vecs,
+                        const DotRoom& room) {
+  const RotPlan none{0, 0};
+  if (r < 27 || r > 31 || room.cus <= 0) return none;
+  for (uint32_t i = 1; i < r; ++i)
+    if (rot[i] != rot[0] + int(i)) return none;
+  RotPlan best = none;
+  uint64_t least = rot_rounds_cost(q_all, r, n_all, vecs, room);
+  const uint32_t over = q_all % kPairQueries;
+  for (int less = 0; less < 2; ++less) {
+    if (less && (over == 0 || over > kPairQueries / 2)) break;
+    const uint32_t q = less ? q_all - over : q_all;
+    if (q == 0) break;
+    const uint64_t per = uint64_t(q + kPairQueries - 1) / kPairQueries * vecs, nt = (n_all + kRotCols - 1) / kRotCols;
+    const uint64_t full = full_cols(n_all, per, room);
+    for (int part = 0; part < 2; ++part) {
+      const uint64_t cols = part ? full : nt;
+      if (cols == 0 || (part && cols == nt)) break;
+      const uint64_t n = cols * kRotCols < n_all ? cols * kRotCols : n_all;
+      const uint64_t cost = kLaunchCost + pair_tile_cost(q) * ((cols * per + room.cus - 1) / room.cus) +
+                            rot_rounds_cost(q, r, n_all - n, vecs, room) +
+                            rot_rounds_cost(q_all - q, r, n_all, vecs, room);
+      if (cost < least) {
+        least = cost;
+        best = RotPlan{q, n};
+      }
+    }
+  }
+  return best;
 }
 
 }  // namespace imc

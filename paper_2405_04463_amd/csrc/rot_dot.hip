@@ -458,20 +458,6 @@ __global__ void __launch_bounds__(kRotThreads) rot_dot_groups_kernel(RotGroupsAr
   }
 }
 
-// Row tiles of a launch that go first: all but a last one of up to 128 rows,
-// whose workgroups are the shorter ones, so that they fill the ends of the CUs'
-// work; in the column tiles' order they would keep the longer tiles of a
-// column apart.  A launch of many rounds has no ends to fill and reads the
-// database once less in one order.  us, in order / apart, 65,536 entries, 15
-// rotations: 18 queries 3,599 / 3,214, 40 5,676 / 5,397, 52 7,247 / 6,920, 70
-// (20 rounds of one tile per CU) 8,987 / 8,798; last tiles of 163 and 192
-// rows no better (5,979 / 6,004, 7,706 / 7,948); 40 queries against 300,000
-// (55 rounds) 24,718 / 24,911, 64 x 17 against 100,000 (31) 13,733 / 13,981.
-uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles) {
-  const uint32_t mt = uint32_t((rows + kRotM - 1) / kRotM);
-  return mt > 1 && rows - uint64_t(mt - 1) * kRotM <= 128 && tiles <= 24 * 256 ? mt - 1 : mt;
-}
-
 // The query slots of a 256-row tile (ceil(256 / r) + 1 of them) must fit the
 // A staging of the configuration: 3 chunks per thread up to 13 queries (r >= 22),
 // 5 up to 22 queries (r >= 13, default configuration only).
@@ -873,22 +859,22 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
   d.b_blocks = (n + 31) / 32;
   d.n = n;
   d.nt = uint32_t((n + kBN - 1) / kBN);
-  // one workgroup per CU (its LDS): split the segments while CUs are left over
   constexpr uint32_t kSegs = Geo<K>::kChunks / 2 / kSegSteps;
-  const uint64_t cols = uint64_t(d.nt) * (mask ? 2 : 1);
-  const uint32_t splits = dot_splits((rows + kBM - 1) / kBM * cols, 1, kSegs, rows * n * (mask ? 2 : 1), scratch);
-  d.tile_m = splits > 1 ? kBM : rot_tile_rows(rows, d.nt, mask ? 2 : 1, scratch.cus);
+  static_assert(kSegs == rot_segs(K == kKGalois), "the plan's parts are the launch's");
+  const uint32_t vecs = mask ? 2 : 1;
+  const uint32_t splits = rot_splits(rows, n, vecs, dot_room(scratch, K == kKGalois));
+  d.seg_per = (kSegs + splits - 1) / splits;
+  d.splits = (kSegs + d.seg_per - 1) / d.seg_per;
+  d.tile_m = d.splits > 1 ? kBM : rot_tile_rows(rows, d.nt, vecs, scratch.cus);
   d.mt = (rows + d.tile_m - 1) / d.tile_m;
   d.max_q = (d.tile_m + r - 1) / r + 1;
   if (int(d.max_q) * 2 * kSegChunks > ACH * kThreads) return hipErrorInvalidValue;
   for (int i = 0; i < IMC_MAX_ROT_DEV; ++i) d.rot[i] = i < int(r) ? rot[i] : 0;
   const uint32_t ntg = (d.nt + 7) / 8;
   if (uint64_t(ntg) * 8 * d.mt > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const dim3 grid(ntg * 8 * d.mt, 1, mask ? 2 : 1);   // z: code, mask
+  const dim3 grid(ntg * 8 * d.mt, 1, vecs);   // z: code, mask
   const size_t lds = 3 * size_t(kRotStage) + 2 * size_t(d.max_q) * 2 * kSegBytes;
-  if (splits > 1) {
-    d.seg_per = (kSegs + splits - 1) / splits;
-    d.splits = (kSegs + d.seg_per - 1) / d.seg_per;
+  if (d.splits > 1) {
     d.part = scratch.part;
     auto kern = rot_dot_split_kernel<K, ACH>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -901,9 +887,8 @@ static hipError_t launch_rot_cfg(const int8_t* qop, const uint32_t* qidx, uint32
     if (e != hipSuccess) return e;
     return launch_reduce_parts(scratch, d.splits, rows, n, code, mask, ld, s);
   }
-  d.splits = d.seg_per = 0;
   d.part = nullptr;
-  d.lead = d.tile_m < kRotM ? d.mt : rot_lead_tiles(rows, d.mt * cols);
+  d.lead = d.tile_m < kRotM ? d.mt : rot_lead_tiles(rows, uint64_t(d.mt) * d.nt * vecs, scratch.cus);
   auto kern = rot_dot_kernel<K, ACH>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));

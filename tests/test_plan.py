@@ -1,51 +1,27 @@
 """The host-side rules of the dot calls (csrc/plan.h), compiled here without a GPU."""
-import ctypes
-import os
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SHIM = """
-#include "plan.h"
-extern "C" {
-int lends(int owned, uintptr_t stream, uintptr_t to, int per_thread, int capturing) {
-  imc::PartsOwner o;
-  o.owned = owned;
-  o.stream = stream;
-  return o.lends(to, per_thread, capturing);
-}
-unsigned splits(uint64_t tiles, unsigned per_cu, unsigned units, uint64_t outputs, size_t bytes, int cus) {
-  return imc::dot_splits(tiles, per_cu, units, outputs, bytes, cus);
-}
-unsigned tile_rows(uint64_t rows, uint64_t nt, unsigned vecs, int cus) { return imc::rot_tile_rows(rows, nt, vecs, cus); }
-}
-"""
+from planlib import SCRATCH, Plan
 
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    src, out = d / "shim.cpp", d / "shim.so"
-    src.write_text(SHIM)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
-                    os.path.join(ROOT, "paper_2405_04463_amd", "csrc"), str(src), "-o", str(out)], check=True)
-    return ctypes.CDLL(str(out))
+    return Plan(str(tmp_path_factory.mktemp("plan")))
 
 
 def test_parts_are_lent_to_one_stream_only(plan):
-    u = ctypes.c_void_p
-    assert plan.lends(0, u(0), u(5), 0, 0) == 1          # nobody's yet
-    assert plan.lends(1, u(5), u(5), 0, 0) == 1
-    assert plan.lends(1, u(5), u(6), 0, 0) == 0
-    assert plan.lends(1, u(0), u(0), 0, 0) == 1          # the default stream
+    f = plan.L.lends
+    assert f(0, 0, 5, 0, 0) == 1          # nobody's yet
+    assert f(1, 5, 5, 0, 0) == 1
+    assert f(1, 5, 6, 0, 0) == 0
+    assert f(1, 0, 0, 0, 0) == 1          # the default stream
     for owned, of in ((0, 0), (1, 2)):
-        assert plan.lends(owned, u(of), u(2), 1, 0) == 0  # one handle, a stream in every thread
-        assert plan.lends(owned, u(of), u(2), 0, 1) == 0  # captured
+        assert f(owned, of, 2, 1, 0) == 0  # one handle, a stream in every thread
+        assert f(owned, of, 2, 0, 1) == 0  # captured
 
 
 def test_splits_stay_within_the_loop_the_cus_and_the_scratch(plan):
-    f = lambda *a: plan.splits(ctypes.c_uint64(a[0]), a[1], a[2], ctypes.c_uint64(a[3]), ctypes.c_size_t(a[4]), a[5])  # noqa: E731
+    f = plan.L.splits
     assert f(16, 1, 32, 1000, 1 << 25, 256) == 16
     assert f(2, 1, 32, 1000, 1 << 25, 256) == 32         # the loop's pieces
     assert f(2, 2, 80, 1000, 1 << 25, 256) == 80
@@ -57,7 +33,7 @@ def test_splits_stay_within_the_loop_the_cus_and_the_scratch(plan):
 
 def test_rows_of_a_rotation_tile(plan):
     """The fewest rows at which all tiles run at once, a column tile's on one of 8 XCDs."""
-    f = lambda rows, nt, vecs, cus=256: plan.tile_rows(ctypes.c_uint64(rows), ctypes.c_uint64(nt), vecs, cus)  # noqa: E731
+    f = lambda rows, nt, vecs, cus=256: plan.L.tile_rows(rows, nt, vecs, cus)  # noqa: E731
     assert f(31, 8, 2) == 64 and f(247, 1, 2) == 64
     assert f(1024, 1, 2) == 64 and f(1025, 1, 2) == 128   # 32 CUs of one XCD: 16 tiles a vector
     assert f(1025, 1, 1) == 64 and f(2049, 8, 1) == 128
@@ -65,3 +41,32 @@ def test_rows_of_a_rotation_tile(plan):
     assert f(104, 40, 1) == 64 and f(260, 40, 2) == 128
     assert f(200, 129, 2) == 256 and f(128, 65, 2) == 128 and f(128, 129, 2) == 256
     assert f(31, 8, 2, 8) == 256 and f(31, 8, 2, 16) == 64 and f(31, 8, 2, 0) == 256
+
+
+def test_the_plan_and_the_launch_split_by_one_rule(plan):
+    """One tile of 31 rows over 128 entries: 32 parts of the replicated loop, of which the
+    plan counts 16, 16 of the Galois one; 20 tiles in 12 parts either way."""
+    assert plan.L.rot_splits(31, 128, 1, SCRATCH, 256, 0) == 32
+    assert plan.L.rot_splits(31, 128, 1, SCRATCH, 256, 1) == 16
+    for galois in (0, 1):
+        assert plan.L.rot_cost(1, 31, 128, 1, SCRATCH, 256, galois) == 2 * 2 + 56 // 16 + 2
+        assert plan.L.rot_splits(31, 1280, 2, SCRATCH, 256, galois) == 12
+        assert plan.L.rot_cost(1, 31, 1280, 2, SCRATCH, 256, galois) == 2 * 2 + 56 // 12 + 2
+        assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 2 + 56        # not lent: a 64-row tile
+
+
+def test_rounds_are_those_of_the_device(plan):
+    """A last row tile goes apart up to 24 rounds of one tile per CU, however many CUs."""
+    for cus in (32, 64, 256):
+        assert plan.L.lead_tiles(260, 24 * cus, cus) == 1 and plan.L.lead_tiles(260, 24 * cus + 1, cus) == 2
+    assert plan.L.lead_tiles(256, 100, 256) == 1 and plan.L.lead_tiles(385, 100, 256) == 2
+
+
+def test_only_consecutive_lists_go_in_pairs(plan):
+    rot = list(range(-15, 16))
+    assert plan.plan(64, rot, 300_000) == (64, 299_008)
+    assert plan.plan(64, rot, 300_000, scratch=0)[0] == 64                # captured: the same kernels, none split
+    assert plan.plan(64, rot[::-1], 300_000) == (0, 0)
+    assert plan.plan(64, rot[:26], 300_000) == (0, 0) and plan.plan(64, rot[:27], 300_000)[0] == 64
+    assert plan.plan(64, rot[:-1] + [14], 300_000) == (0, 0)
+    assert plan.plan(1, rot, 65_536) == (0, 0) and plan.plan(64, rot, 64) == (0, 0)
