@@ -16,8 +16,11 @@ FLAGS = [
     # keep the compiler from forming packed-FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
-# The pair kernel's loop needs 240 of its 256 registers: with the default
-# order of local assignments the compiler spills inside the loop.
+# The pair kernel takes all of its 256 registers.  With the default order of
+# local assignments the compiler spills 63 (replicated) and 78 (Galois) of them,
+# 41 and 45 instructions of it in the first pass's loop over the query staging;
+# with this order 27 and 28, none of it in those loops and up to 8 instructions a
+# segment of 1,200 MFMAs in the third pass's database staging.
 FILE_FLAGS = {"pair_dot.hip": ["-mllvm", "-greedy-reverse-local-assignment=1"]}
 
 

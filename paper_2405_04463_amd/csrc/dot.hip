@@ -263,7 +263,6 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) dot_kernel(DotArgs arg
 #undef IMC_FRAGS
 #undef IMC_GLOAD
 #undef IMC_LSTORE
-#undef IMC_COMPUTE
 
   // Epilogue: 32x32 block, lane l holds column l%32, register e holds row
   // 8*(e/4) + 4*(l/32) + e%4.
@@ -577,12 +576,12 @@ static hipError_t launch_tiles(DotKernel kern, DotKernel split, uint32_t bm, uin
 
 template <int K, int WM, int WN, int WAVES_M, int WAVES_N, int NSETS>
 static hipError_t launch_dot_cfg(const DotArgs& d, uint32_t rows, uint64_t n, hipStream_t s, bool persistent,
-                                 const DotScratch& scratch, uint32_t per_cu = 1) {
+                                 const DotScratch& scratch) {
   using C = DotCfg<WM, WN, WAVES_M, WAVES_N>;
   static_assert(10 % NSETS == 0, "a piece is whole unrolled iterations");
   return launch_tiles(dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS>,
                       dot_kernel<K, WM, WN, WAVES_M, WAVES_N, NSETS, true>, C::kBM, C::kBN, C::kThreads,
-                      3 * size_t(C::kStageBytes), Geo<K>::kChunks / 2, 10, d, rows, n, s, persistent, scratch, per_cu);
+                      3 * size_t(C::kStageBytes), Geo<K>::kChunks / 2, 10, d, rows, n, s, persistent, scratch, 1);
 }
 
 template <int K, int NX>

@@ -96,6 +96,11 @@ __device__ __forceinline__ uint32_t next_lane(int v) {
   return uint32_t(__builtin_amdgcn_update_dpp(0, v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false));
 }
 
+template <typename F, int... T>
+__device__ __forceinline__ void for_each_step(const F& step, std::integer_sequence<int, T...>) {
+  (step(std::integral_constant<int, T>{}), ...);
+}
+
 // The three products in turn.  PH 0: x against y[c] + y[c + 4]; 1: D against
 // y[c + 4]; 2: D (4 columns earlier) against y[c].
 template <int PH, int K, bool LIVE, bool DBS>
@@ -373,9 +378,7 @@ __device__ __forceinline__ void pair_phase(const PairDotArgs& args, const int8_t
       }
       __syncthreads();
     };
-    [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
-      (step(std::integral_constant<int, T>{}), ...);
-    }(std::make_integer_sequence<int, kT>{});
+    for_each_step(step, std::make_integer_sequence<int, kT>{});
   }
 #undef IMC_SGB
 #undef IMC_BLOAD
