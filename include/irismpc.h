@@ -66,12 +66,17 @@ typedef int imc_status;
                                             EXPANDED_256x128 */
 #define IMC_DOT_TILES_EXPANDED_256x128 1 /* rotated rows expanded into scratch; 256 x 128 tiles,
                                             8 waves of 64 x 64, global loads 4 K-steps of 64
-                                            bytes ahead; smaller tiles for up to 128 rows */
-#define IMC_DOT_TILES_EXPANDED_128x128 2 /* as 1 with 128 x 128 tiles, 4 waves */
-#define IMC_DOT_TILES_EXPANDED_SHALLOW 3 /* 256 x 128 tiles, K-steps of 32 bytes loaded 3 ahead */
-#define IMC_DOT_TILES_ROTATION 4         /* 256 x 128 tiles; each tile's queries staged unrotated in
-                                            LDS per 800-byte segment, rotations read in place
-                                            (used when r >= 13, else as AUTO) */
+                                            bytes ahead; tiles of 64, 128 or 192 rows for calls
+                                            of up to 192, and for up to 128 rows past the last
+                                            whole tile when those make a tile for every CU */
+#define IMC_DOT_TILES_EXPANDED_128x128 2 /* 128 x 128 tiles, 4 waves of 64 x 64 in 32 x 32 x 32
+                                            MFMAs, K-steps of 32 bytes loaded 4 ahead */
+#define IMC_DOT_TILES_EXPANDED_SHALLOW 3 /* the same MFMAs in 256 x 128 tiles of 8 waves, K-steps of
+                                            32 bytes loaded 3 ahead */
+#define IMC_DOT_TILES_ROTATION 4         /* 256 x 128 tiles (of fewer rows when tiles are few); each
+                                            tile's queries staged unrotated in LDS per 800-byte
+                                            segment, rotations read in place (used when r >= 13,
+                                            else as AUTO) */
                                          /* 5: not used */
 #define IMC_DOT_TILES_ROTATION_LDSCOPY 6 /* as 4 with both operands copied from HBM straight into
                                             LDS (8 database stages, no staging registers);

@@ -104,9 +104,9 @@ __device__ __forceinline__ void ml_mfma(v4f (&acc)[4][4], const v4i (&x)[4], con
 // it, so the four MFMAs of a 16-byte piece take bits 0, 1, 2 and 3 of its
 // 4-bit groups: one AND per operand register, no unpacking.  Consecutive
 // workgroups of one XCD walk the row tiles of one entry tile.  Bound by issue:
-// 160 ANDs and 64 MFMAs of 16 cycles a piece.  1,984 rows x 65,536 entries
-// 3,170 -> 575 us (popcounts on the vector ALUs before); 31 rows x 1,000
-// entries 91 -> 26.  Without the scheduling fences the compiler moves the next
+// 160 ANDs and 64 MFMAs of 16 cycles a piece (1,984 rows x 300,000 entries: MFMA
+// pipes 0.60 busy at 2.1 GHz).  1,984 rows x 65,536 entries 3,170 -> 575 us
+// (popcounts on the vector ALUs before); 31 rows x 1,000 entries 91 -> 26.  Without the scheduling fences the compiler moves the next
 // piece's loads behind the MFMAs: 710 us, 850 without unrolling.
 __global__ void __launch_bounds__(256) plain_ml_kernel(MlArgs a) {
   const uint32_t i = blockIdx.x, xcd = i & 7, s8 = i >> 3;

@@ -25,18 +25,18 @@ namespace imc {
 //
 // What bounds it: power (and up to 64 rows, memory).  On random bytes a
 // register-only loop of 16 x 16 x 64 MFMAs runs at 4.0 POP/s on this part, one
-// of 32 x 32 x 32 at 3.35; with the staging and the LDS reads the clock is at
-// 1.5 - 2.0 GHz and the MFMA pipes 0.46 - 0.57 busy.  One party's dots against
-// 65,536 entries, ms, with 32 x 32 x 32 MFMAs and 64 rows per wave at any row
-// count / as it stands: 1 query of 31 rotations 1.21 / 1.08 (5.7 GB/ms), 4:
-// 1.52 / 1.42, 8: 2.32 / 2.11, 16 of 15: 2.39 / 2.18, 40 of 15: 5.95 / 5.39,
-// 64 of 15: 8.16 / 7.71, 64 of 24: 12.2 / 11.1.  Scheduling groups that spread
-// the LDS reads over the MFMAs, and slot strides that keep two queries' rows
-// in different banks, change nothing.  The next step's query fragments are read
-// under the last two of its four groups of MFMAs: all of them under the last
-// one left a launch of one tile per CU waiting at the barrier (19 queries of
-// 13 rotations x 64 entries, 256-row tiles: 409 us, then 391; 40 queries of 15
-// x 65,536, on one box: 5.48 ms, then 5.34).
+// of 32 x 32 x 32 at 3.35; 64 queries of 31 rotations against 300,000 entries run
+// at 2.0 GHz with the MFMA pipes 0.64 busy and the LDS 0.49, a fifth of that bank
+// conflicts of the rotated query reads.  One party's dots against 65,536 entries,
+// ms, with 32 x 32 x 32 MFMAs and 64 rows per wave at any row count / as it
+// stands: 1 query of 31 rotations 1.15 / 1.08 (6.2 GB/ms), 12 of 15: 2.03 / 1.78,
+// 40 of 15: 5.90 / 5.34, 70 of 15: 9.56 / 8.67, 64 of 24: 12.2 / 11.3.
+// Scheduling groups that spread the LDS reads over the MFMAs, and slot strides
+// that keep two queries' rows in different banks, change nothing.  The next
+// step's query fragments are read under the last two of its four groups of
+// MFMAs: all of them under the last one left a launch of one tile per CU waiting
+// at the barrier (19 queries of 13 rotations x 64 entries, 256-row tiles: 409 us,
+// then 391; 40 of 15 x 65,536, on one box: 5.48 ms, then 5.34).
 // ---------------------------------------------------------------------------
 struct RotDotArgs {
   const int8_t* qop;     // unrotated query operand, row-major [q][plane 4][K]
@@ -387,7 +387,7 @@ __global__ void __launch_bounds__(kRotThreads) rot_dot_kernel(RotDotArgs args) {
 
 // The same with a tile's segments split over args.splits workgroups, for
 // calls with fewer tiles than CUs: their time is that of one workgroup's
-// serial K loop, 0.7 us a step with up to 64 rows and 1.3 with all 256 (400
+// serial K loop, 0.5 us a step with up to 64 rows and 1.0 with all 256 (400
 // steps), at whatever size.  Each part's sums go to scratch as u32 and
 // reduce_parts_kernel adds them.  31 rows x 1,000 entries: 209 -> 25 us;
 // 1,984 rows x 64 entries: 394 -> 43 us; 93 rows x 4,000: 244 -> 90.
