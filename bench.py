@@ -37,7 +37,7 @@ MFMA_I8_PEAK_TOPS = 5000.0      # MI355X dense int8, tera-ops/s (MAC = 2 ops)
 # alone.  Valid only for the sources that choose, launch and are these kernels.
 CALL_SOURCES = {
     "paper_2405_04463_amd/csrc/pair_dot.hip":
-        "e1528b8d55bf4c378ad527c504d0d1f8ea5422727393b110cbc973ce9d2988ce",
+        "978923b1838cf7ab72537f6f12ead2d79977cd061e553b9e5ceebbe2be5b7fab",
     "paper_2405_04463_amd/csrc/rot_dot.hip":
         "75733a9f35e3a6d0da6c96701020f15aa0ed4ccdf17ed3674ae33ea94b5f42f0",
     "paper_2405_04463_amd/csrc/dot.hip":

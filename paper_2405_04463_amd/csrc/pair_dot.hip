@@ -27,7 +27,7 @@
 // the clock down to 1.7 - 2.0 GHz, the 16 x 16 x 64 shape less.  One party's
 // dots of 64 queries x 31 rotations against 65,536 entries: 15.8 ms with
 // rot_dot.hip's kernel, 12.9 with this scheme on 32 x 32 x 32 MFMAs, 11.2 as
-// it stands.  Against 300,000 entries: MFMA pipes 0.71 busy at 1.8 GHz, 69.7 GB
+// it stands.  Against 300,000 entries: MFMA pipes 0.70 busy at 1.8 GHz, 69.7 GB
 // read (each product streams its half of the database tile).  Without any
 // staging the loops take 8.5 ms of the 11.2.
 #include <utility>
