@@ -43,11 +43,11 @@ CALL_SOURCES = {
     "paper_2405_04463_amd/csrc/dot.hip":
         "0309f71efd77328845d4d98af76bf502ce7af1f652d8ce2cc79ea12d00d9a29d",
     "paper_2405_04463_amd/csrc/plan.h":
-        "a63240a57678c43b072e683c9207db22f2767484c4d1ea0f44b9ccddbfc442e0",
+        "75566056833cee0b1adc73d11449f822e41351425ab766c8a331dc56cc9b5df7",
     "paper_2405_04463_amd/csrc/launch.h":
         "75a2832985b8a536ccddcbdf5c8041df22fbb8ca423d9a55465ea0f1d39f96ee",
     "paper_2405_04463_amd/csrc/api.cpp":
-        "a9a4de9d7004f13ab94ae12320dcead519c1342a528286c94ae9d0d8992334aa",
+        "99f06a014413c4ce5df28988f35bdf4ca9f8dca5192c5fa65526bac0ee7ec1ab",
     "paper_2405_04463_amd/csrc/device.h":
         "4c1a3b4ab4b31d959d8bad5a27477516a04872568ad8d0abc29b0de3c59b9f10",
 }

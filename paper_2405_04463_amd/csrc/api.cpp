@@ -97,17 +97,22 @@ imc_status check_ids(const imc_ids* ids) {
 // Where it is not lent, the call does not split.
 class PartsLease {
  public:
-  PartsLease(imc_ctx* c, hipStream_t stream) : lock_(c->parts_mu) {
+  PartsLease(imc_ctx* c, hipStream_t stream) : lock_(c->parts_mu, std::defer_lock) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     const bool known = hipStreamIsCapturing(stream, &st) == hipSuccess;
     if (!known) (void)hipGetLastError();
+    const auto lent = [&] {
+      return c->owner.lends(reinterpret_cast<uintptr_t>(stream), stream == hipStreamPerThread,
+                            !known || st != hipStreamCaptureStatusNone);
+    };
     scratch = c->parts;
-    if (!c->owner.lends(reinterpret_cast<uintptr_t>(stream), stream == hipStreamPerThread,
-                        !known || st != hipStreamCaptureStatusNone)) {
-      scratch.part = nullptr;
-      scratch.bytes = 0;
+    if (lent()) {                 // the others never wait for the one who enqueues
+      lock_.lock();
+      if (lent()) return;         // nobody took it meanwhile
       lock_.unlock();
     }
+    scratch.part = nullptr;
+    scratch.bytes = 0;
   }
   imc::DotScratch scratch;
 

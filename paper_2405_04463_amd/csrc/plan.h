@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace imc {
 
 // Which stream may use a context's parts scratch: the first whose call splits a
@@ -14,14 +16,14 @@ namespace imc {
 // eager calls) nor to the per-thread default stream, whose one handle names
 // another stream in every thread.
 struct PartsOwner {
-  bool owned = false;
-  uintptr_t stream = 0;
+  std::atomic<bool> owned{false};
+  std::atomic<uintptr_t> stream{0};   // valid once owned
   bool lends(uintptr_t to, bool per_thread, bool capturing) const {
     return !capturing && !per_thread && (!owned || stream == to);
   }
-  void take(uintptr_t by) {
-    owned = true;
+  void take(uintptr_t by) {   // one caller at a time
     stream = by;
+    owned = true;
   }
 };
 
