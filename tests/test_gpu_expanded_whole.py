@@ -91,3 +91,24 @@ def test_persistent_grid(keys, q, r, n, galois):
             assert torch.equal(g, p), tiles
             assert np.array_equal(g[:, at].cpu().numpy().view(np.uint16), w), tiles
     ctx.close()
+
+
+@pytest.mark.parametrize("q,r,n,first,galois,mask", [
+    (33, 8, 16400, 64, False, True),     # 264 rows: 8 in a launch of their own
+    (64, 5, 16390, 0, True, True),       # 320: 64
+    (64, 6, 16385, 0, True, True),       # 384: 128
+    (35, 11, 16385, 0, True, False),     # 385: 129, in the second tile
+    (48, 4, 16385, 0, False, True),      # one 192-row tile
+    (43, 3, 16385, 64, True, True),      # 129 rows in one
+    (19, 5, 16400, 0, True, True),       # 95 in a 128-row tile
+])
+def test_rows_past_the_last_tile_against_oracle(keys, q, r, n, first, galois, mask):
+    rot = [((7 * i) % 31) - 15 for i in range(r)]
+    imc, ctx, ref, call = _setup(keys, q, n, first, galois, q * r)
+    at = torch.tensor([0, 127, 128, n // 2, n - 1]).cuda()
+    got = call(imc.DOT_TILES_EXPANDED_256x128, torch.cuda.current_stream(), rot, n, n + 3, mask)
+    for g, w in zip(got, ref(rot, [(e, e + 1) for e in at.tolist()])):
+        if g is not None:
+            assert np.array_equal(g[:, at].cpu().numpy().view(np.uint16), w)
+            assert (g[:, n:] == 7).all()
+    ctx.close()
