@@ -41,9 +41,9 @@ CALL_SOURCES = {
     "paper_2405_04463_amd/csrc/rot_dot.hip":
         "75733a9f35e3a6d0da6c96701020f15aa0ed4ccdf17ed3674ae33ea94b5f42f0",
     "paper_2405_04463_amd/csrc/dot.hip":
-        "0309f71efd77328845d4d98af76bf502ce7af1f652d8ce2cc79ea12d00d9a29d",
+        "c291e6983b90fa3d0d4d2fbb6d22aec324b54b9d46b2a1a793346d3d04b0b645",
     "paper_2405_04463_amd/csrc/plan.h":
-        "75566056833cee0b1adc73d11449f822e41351425ab766c8a331dc56cc9b5df7",
+        "1e160d042d1dcf0a604a2b2d90b703766e143f3a5f0be229e67bbfc396674496",
     "paper_2405_04463_amd/csrc/launch.h":
         "75a2832985b8a536ccddcbdf5c8041df22fbb8ca423d9a55465ea0f1d39f96ee",
     "paper_2405_04463_amd/csrc/api.cpp":

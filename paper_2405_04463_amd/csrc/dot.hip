@@ -513,8 +513,8 @@ hipError_t launch_reduce_parts(const DotScratch& scratch, uint32_t splits, uint6
   const uint64_t count = rows * n;
   if (!fits_grid(count, 256)) return hipErrorInvalidValue;
   // The launch records the event itself: 64 queries x 31 rotations x 64 entries
-  // take 43.5 us with it and without one, 45.2 with a record of its own, 45.5
-  // with a system-scope fence.
+  // take 43.5 us with it and without one (2 us more where each call is waited
+  // for), 45.2 with a record of its own, 45.5 with a system-scope fence.
   const uint32_t* part = scratch.part;
   void* args[] = {&part, &splits, const_cast<uint64_t*>(&count), &n, &code, &mask, &ld};
   return hipExtLaunchKernel(reinterpret_cast<const void*>(reduce_parts_kernel),

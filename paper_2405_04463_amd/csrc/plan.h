@@ -117,13 +117,16 @@ inline uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 142 : q > 12 ? 168 
 // speed.
 constexpr uint32_t kPlanSplits = 16;
 
+// The shorter tiles of few that all run at once are not counted here: the model
+// would take the last round of calls that don't split apart, which then waits for
+// the rounds before it (us, whole / apart: 56 queries of 26 rotations x 46,052
+// entries 3,978 / 4,351, 44 of 15 x 23,261 Galois 618 / 664, 13 of 31 x 17,337 578 /
+// 627).
 inline uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
   if (q == 0 || n == 0) return 0;
-  const uint64_t rows = q * r, nt = (n + kRotCols - 1) / kRotCols, mt = rot_tiles(rows, 256), cols = nt * vecs;
+  const uint64_t rows = q * r, mt = rot_tiles(rows, 256), cols = (n + kRotCols - 1) / kRotCols * vecs;
   const uint32_t splits = rot_splits(rows, n, vecs, room);
   if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / (splits < kPlanSplits ? splits : kPlanSplits) + 2;
-  const uint32_t m = rot_tile_rows(rows, nt, vecs, room.cus);
-  if (m < 256) return kLaunchCost + rot_tile_cost(m);
   const auto rounds = [&](uint64_t tiles) { return (tiles + room.cus - 1) / room.cus; };
   const uint64_t lead = rot_lead_tiles(rows, mt * cols, room.cus);
   return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +
@@ -152,6 +155,12 @@ inline uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vec
   return rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room);
 }
 
+// A call that runs whole in shorter tiles, all at once; none if that is not so.
+inline uint64_t rot_short_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
+  const uint32_t m = rot_tile_rows(q * r, (n + kRotCols - 1) / kRotCols, vecs, room.cus);
+  return m < 256 && rot_splits(q * r, n, vecs, room) == 1 ? kLaunchCost + rot_tile_cost(m) : UINT64_MAX;
+}
+
 struct RotPlan {
   uint32_t q;   // queries and columns of the pairs; the rest is rot_dot.hip's
   uint64_t n;
@@ -165,7 +174,11 @@ inline RotPlan rot_plan(uint32_t q_all, uint32_t r, const int8_t* rot, uint64_t 
   for (uint32_t i = 1; i < r; ++i)
     if (rot[i] != rot[0] + int(i)) return none;
   RotPlan best = none;
+  // us, pairs / shorter tiles: 9 queries of 30 rotations x 632 entries Galois 264 /
+  // 103, 28 of 30 x 1,405 507 / 196
   uint64_t least = rot_rounds_cost(q_all, r, n_all, vecs, room);
+  const uint64_t in_short_tiles = rot_short_cost(q_all, r, n_all, vecs, room);
+  least = in_short_tiles < least ? in_short_tiles : least;
   const uint32_t over = q_all % kPairQueries;
   for (int less = 0; less < 2; ++less) {
     if (less && (over == 0 || over > kPairQueries / 2)) break;

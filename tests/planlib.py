@@ -24,6 +24,9 @@ unsigned rot_splits(uint64_t rows, uint64_t n, unsigned vecs, size_t bytes, int 
 uint64_t rot_cost(uint64_t q, unsigned r, uint64_t n, unsigned vecs, size_t bytes, int cus, int galois) {
   return imc::rot_cost(q, r, n, vecs, imc::DotRoom{bytes, cus, imc::rot_segs(galois)});
 }
+uint64_t first_cols(uint64_t q, unsigned r, uint64_t n, unsigned vecs, size_t bytes, int cus, int galois) {
+  return imc::rot_first_cols(q, r, n, vecs, imc::DotRoom{bytes, cus, imc::rot_segs(galois)});
+}
 void plan(unsigned q, unsigned r, const int8_t* rot, uint64_t n, unsigned vecs, size_t bytes, int cus, int galois,
           uint64_t out[2]) {
   const imc::RotPlan p = imc::rot_plan(q, r, rot, n, vecs, imc::DotRoom{bytes, cus, imc::rot_segs(galois)});
@@ -53,6 +56,7 @@ class Plan:
         L.rot_splits.argtypes = [u64, u64, u32, sz, i, i]
         L.rot_cost.argtypes = [u64, u32, u64, u32, sz, i, i]
         L.rot_cost.restype = u64
+        L.first_cols.argtypes, L.first_cols.restype = L.rot_cost.argtypes, u64
         L.plan.argtypes = [u32, u32, ctypes.c_char_p, u64, u32, sz, i, i, ctypes.POINTER(u64)]
 
     def plan(self, q, rot, n, vecs=2, galois=False, scratch=SCRATCH, cus=256):

@@ -52,7 +52,7 @@ def test_the_plan_and_the_launch_split_by_one_rule(plan):
         assert plan.L.rot_cost(1, 31, 128, 1, SCRATCH, 256, galois) == 2 * 2 + 56 // 16 + 2
         assert plan.L.rot_splits(31, 1280, 2, SCRATCH, 256, galois) == 12
         assert plan.L.rot_cost(1, 31, 1280, 2, SCRATCH, 256, galois) == 2 * 2 + 56 // 12 + 2
-        assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 2 + 56        # not lent: a 64-row tile
+        assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 2 + 56        # not lent
 
 
 def test_rounds_are_those_of_the_device(plan):
@@ -60,6 +60,22 @@ def test_rounds_are_those_of_the_device(plan):
     for cus in (32, 64, 256):
         assert plan.L.lead_tiles(260, 24 * cus, cus) == 1 and plan.L.lead_tiles(260, 24 * cus + 1, cus) == 2
     assert plan.L.lead_tiles(256, 100, 256) == 1 and plan.L.lead_tiles(385, 100, 256) == 2
+
+
+def test_a_whole_loop_keeps_its_last_round(plan):
+    """Not lent: 44 queries of 15 rotations against 23,261 entries, three tiles of rows and 182 of
+    columns, are 2.1 rounds; the last 0.1 in a call of its own would wait for the rounds before it."""
+    f = lambda q, r, n, v, scratch: plan.L.first_cols(q, r, n, v, scratch, 256, 0)  # noqa: E731
+    assert f(44, 15, 23_261, 1, 0) == 23_261 and f(56, 26, 46_052, 1, 0) == 46_052
+    assert f(44, 15, 23_261, 1, SCRATCH) < 23_261            # its loop splits: worth a call
+
+
+def test_few_tiles_of_a_whole_loop_stay_on_the_rotation_kernel(plan):
+    """Not lent, and all of its 64- or 128-row tiles at once: a tile of pairs takes longer than one of those."""
+    rot = list(range(-15, 15))
+    for q, n, galois in ((9, 632, True), (28, 1405, False), (16, 1000, False), (64, 64, True)):
+        assert plan.plan(q, rot, n, 2, galois, scratch=0) == (0, 0), (q, n)
+    assert plan.plan(64, rot, 5000, scratch=0)[0] == 64
 
 
 def test_only_consecutive_lists_go_in_pairs(plan):
