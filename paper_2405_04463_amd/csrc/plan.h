@@ -90,63 +90,112 @@ inline uint32_t rot_lead_tiles(uint64_t rows, uint64_t tiles, int cus) {
 }
 
 // ---------------------------------------------------------------------------
-// Which kernel takes what of a call at r >= 13 rotations.  Times are counted
-// in units of 5 us of the replicated form.  A call takes its tiles in rounds
-// of one per CU; a tile's time, from 65,536 entries (ms / rounds): rot_dot.hip
-// 2 queries 1.14 / 4, 4: 1.42 / 4, 6: 1.75 / 4, 8: 2.11 / 4 (one row tile), 16:
-// 3.90 / 8, 32: 7.45 / 16, 64: 14.5 / 32; pairs 8 queries 2.65 / 4, 10: 3.06 /
-// 4, 12: 3.06 / 4, 16: 3.39 / 4 (one query tile), 32: 5.86 / 8, 64: 10.9 / 16.
-// The last round is rarely full, and up to 8 queries past a multiple of 16
-// leave half of a pairs' tile idle: those columns and those queries may go to
-// rot_dot.hip's kernel in calls of their own, which splits its loop when its
-// tiles are few.  us, one launch / as planned: 16 queries x 20,011 entries
-// 1,370 / 1,097, 18 x 65,536 5,420 / 4,490, 7 queries x 15 rotations x 20,000
-// 585 / 480.
+// Which kernel takes what of a call at r >= 13 rotations.  Times in us of the
+// replicated form (Galois-ring shares take half of each alike).
+//
+// A column tile's workgroups run on one XCD, one to a CU, so a launch runs in
+// rounds of the XCD that has the most column tiles.  A full round takes longer
+// than a sparse one (the part is power-bound: few busy CUs run at a higher clock);
+// up to half of the CUs take no longer than one.  Measured, 31 rotations, one
+// launch, the code dot alone (us; column tiles):
+//   rot_dot.hip   1 query 140 (8) 156 (64) 172 (128) 275 (256) 546 (512), 8 194 (8)
+//     224 (64) 318 (128) 408 (140) 529 (256) 1,061 (512), 16 194 (8) 302 (64) 489 (128)
+//     825 (140) 979 (256), 64 201 (8) 438 (32) 806 (40) 923 (64) 1,242 (72) 1,844 (128);
+//   pair_dot.hip  8 queries 339 (8) 460 (128) 533 (192), 16 506 (8) 572 (128) 705 (192),
+//     32 507 (8) 554 (64) 739 (128) 1,197 (140), 64 508 (8) 698 (64) 1,157 (72) 1,409 (128).
+// The costs below give 1,667 such launches within -8 and +15 % in nine of ten.
+//
+// The last round is rarely full, and up to 8 queries past a multiple of 16 leave
+// half of a pairs' tile idle: those columns and those queries may go to
+// rot_dot.hip's kernel in calls of their own, which splits its loop when its tiles
+// are few.  Columns are taken apart by eights, one for each XCD: 18 of 25 in the
+// first call (80 queries of 22 rotations x 3,133 entries, all CUs counted as one)
+// are two rounds on two of the XCDs, 1,010 us against 825 in one launch.
 // ---------------------------------------------------------------------------
-constexpr uint64_t kLaunchCost = 2;
 constexpr uint32_t kRotCols = 128, kPairQueries = 16;   // entries of a column tile, queries of a pairs' tile
+constexpr uint64_t kLaunchCost = 5;
 
-// A rot_dot.hip tile alone in its columns, and beside others.
-inline uint64_t rot_tile_cost(uint64_t rows) { return rows <= 64 ? 56 : rows <= 128 ? 68 : rows <= 192 ? 86 : 105; }
-constexpr uint64_t kRotSharedCost = 94;
-inline uint64_t pair_tile_cost(uint64_t q) { return q > 16 ? 142 : q > 12 ? 168 : q > 8 ? 153 : 132; }
+struct TileCost {
+  uint64_t sparse, full;   // a round of few tiles, one of a tile on every CU
+};
+// A rot_dot.hip tile of this many rows, alone in its columns.
+inline TileCost rot_tile_cost(uint64_t rows) {
+  return rows <= 32    ? TileCost{140, 275}
+         : rows <= 64  ? TileCost{190, 290}
+         : rows <= 128 ? TileCost{200, 360}
+         : rows <= 192 ? TileCost{235, 440}
+                       : TileCost{310, 530};
+}
+// One beside others of its columns.
+inline TileCost rot_shared_cost(uint32_t m) {
+  return m == 64 ? TileCost{192, 230} : m == 128 ? TileCost{250, 310} : m == 192 ? TileCost{300, 385} : TileCost{310, 475};
+}
+inline TileCost pair_tile_cost(uint64_t q) {
+  return q <= 8 ? TileCost{400, 635} : q <= 12 ? TileCost{490, 765} : q <= 16 ? TileCost{505, 825}
+       : q <= 32 ? TileCost{505, 735} : TileCost{505, 710};
+}
 
-// More parts than these, in replicated calls of up to 8 tiles, save up to 3 of
-// a call's units, which is less than the model is true to: counted, they change
-// the route of 4 in 200,000 random calls, to 1.03, 1.04, 0.64 and 0.66 of the
-// speed.
-constexpr uint32_t kPlanSplits = 16;
+// Column tiles of the XCD that has the most.
+inline uint64_t xcd_cols(uint64_t cols) { return (cols + 7) / 8; }
 
-// The shorter tiles of few that all run at once are not counted here: the model
-// would take the last round of calls that don't split apart, which then waits for
-// the rounds before it (us, whole / apart: 56 queries of 26 rotations x 46,052
-// entries 3,978 / 4,351, 44 of 15 x 23,261 Galois 618 / 664, 13 of 31 x 17,337 578 /
-// 627).
+// `tiles` workgroups on an XCD.
+inline uint64_t rounds_cost(uint64_t tiles, TileCost c, int cus) {
+  const uint64_t cx = uint64_t(cus) / 8, before = (tiles - 1) / cx, last = tiles - before * cx;
+  return before * c.full + c.sparse + (2 * last > cx ? (c.full - c.sparse) * (2 * last - cx) / cx : 0);
+}
+
+// A whole loop in tiles of m rows, `cols` column tiles over all vectors on an XCD.
+inline uint64_t rot_loop_cost(uint64_t rows, uint32_t m, uint64_t cols, int cus) {
+  const uint64_t mt = rot_tiles(rows, m), last = rows - (mt - 1) * m;
+  if (mt == 1) return rounds_cost(cols, rot_tile_cost(last), cus);
+  TileCost c = rot_shared_cost(m);
+  if (m < 256) return rounds_cost(cols * mt, c, cus);
+  const TileCost short_one = rot_tile_cost(last);
+  const uint64_t alone = rot_tile_cost(256).full, cx = uint64_t(cus) / 8;
+  if (last > 128 || cols * mt <= cx) {
+    const uint64_t equal = (cols * (mt - 1) * alone + cols * short_one.full + alone - 1) / alone;
+    return rounds_cost(equal > cx || cols * mt <= cx ? equal : cols * mt, c, cus);
+  }
+  // short last tiles after the others, and beside their last round
+  if (mt == 2) c.full = alone;
+  const uint64_t beside = (cx - cols * (mt - 1) % cx) % cx;
+  return rounds_cost(cols * (mt - 1), c, cus) + (cols > beside ? rounds_cost(cols - beside, short_one, cus) : 0);
+}
+
+// One call of rot_dot.hip's kernel.
 inline uint64_t rot_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
   if (q == 0 || n == 0) return 0;
-  const uint64_t rows = q * r, mt = rot_tiles(rows, 256), cols = (n + kRotCols - 1) / kRotCols * vecs;
+  const uint64_t rows = q * r, nt = (n + kRotCols - 1) / kRotCols;
   const uint32_t splits = rot_splits(rows, n, vecs, room);
-  if (splits > 1) return 2 * kLaunchCost + rot_tile_cost(rows) / (splits < kPlanSplits ? splits : kPlanSplits) + 2;
-  const auto rounds = [&](uint64_t tiles) { return (tiles + room.cus - 1) / room.cus; };
-  const uint64_t lead = rot_lead_tiles(rows, mt * cols, room.cus);
-  return kLaunchCost + (lead > 1 ? kRotSharedCost : rot_tile_cost(rows)) * rounds(lead * cols) +
-         (lead < mt ? rot_tile_cost(rows - lead * 256) * rounds(cols) : 0);
+  if (splits > 1) {
+    const uint32_t per = (room.segs + splits - 1) / splits, parts = (room.segs + per - 1) / per;
+    return 3 * kLaunchCost + rot_loop_cost(rows, 256, xcd_cols(nt * parts) * vecs, room.cus) * per / room.segs;
+  }
+  return kLaunchCost + rot_loop_cost(rows, rot_tile_rows(rows, nt, vecs, room.cus), xcd_cols(nt) * vecs, room.cus);
 }
 
-// Column tiles that fill whole rounds, `per` tiles each.
+// Column tiles whose `per` workgroups each fill whole rounds of every XCD.
 inline uint64_t full_cols(uint64_t n, uint64_t per, const DotRoom& room) {
-  return (n + kRotCols - 1) / kRotCols * per / room.cus * room.cus / per;
+  const uint64_t cx = uint64_t(room.cus) / 8, nt = (n + kRotCols - 1) / kRotCols;
+  return xcd_cols(nt) * per / cx * cx / per * 8;
 }
 
-// rot_dot.hip's columns that go in a first call, the whole rounds; all n of
-// them if the last round is better not taken apart.
+// A call is taken apart when the model gives it 1/24 of the time or 50 us, a tenth of
+// a round: whole rounds cost the same either way, and less is within its error.
+inline bool clearly_less(uint64_t cost, uint64_t than) {
+  const uint64_t margin = than / 24;
+  return cost + (margin < 50 ? margin : 50) < than;
+}
+
+// rot_dot.hip's columns that go in a first call, the whole rounds; all n of them if
+// the last round is better not taken apart, as where its loop would not split (56
+// queries of 26 rotations x 46,052 entries 3,978 us, in two calls 4,351).
 inline uint64_t rot_first_cols(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
-  if (room.cus <= 0) return n;
+  if (room.cus < 8 || q == 0 || n == 0) return n;
   const uint64_t m = full_cols(n, rot_tiles(q * r, 256) * vecs, room) * kRotCols;
-  if (m == 0 || m >= n) return n;
-  return rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room) < rot_cost(q, r, n, vecs, room)
-             ? m
-             : n;
+  if (m == 0 || m >= n || rot_splits(q * r, n - m, vecs, room) < 2) return n;
+  const uint64_t apart = rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room);
+  return clearly_less(apart, rot_cost(q, r, n, vecs, room)) ? m : n;
 }
 
 inline uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
@@ -155,10 +204,11 @@ inline uint64_t rot_rounds_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vec
   return rot_cost(q, r, m, vecs, room) + rot_cost(q, r, n - m, vecs, room);
 }
 
-// A call that runs whole in shorter tiles, all at once; none if that is not so.
-inline uint64_t rot_short_cost(uint64_t q, uint32_t r, uint64_t n, uint32_t vecs, const DotRoom& room) {
-  const uint32_t m = rot_tile_rows(q * r, (n + kRotCols - 1) / kRotCols, vecs, room.cus);
-  return m < 256 && rot_splits(q * r, n, vecs, room) == 1 ? kLaunchCost + rot_tile_cost(m) : UINT64_MAX;
+inline uint64_t pair_cost(uint64_t q, uint64_t cols, uint32_t vecs, const DotRoom& room) {
+  const uint64_t tiles = xcd_cols(cols) * vecs * ((q + kPairQueries - 1) / kPairQueries);
+  TileCost c = pair_tile_cost(q);
+  if (tiles > uint64_t(room.cus) / 8) c.sparse -= 60;   // behind a full round
+  return kLaunchCost + rounds_cost(tiles, c, room.cus);
 }
 
 struct RotPlan {
@@ -170,30 +220,25 @@ struct RotPlan {
 inline RotPlan rot_plan(uint32_t q_all, uint32_t r, const int8_t* rot, uint64_t n_all, uint32_t vecs,
                         const DotRoom& room) {
   const RotPlan none{0, 0};
-  if (r < 27 || r > 31 || room.cus <= 0) return none;
+  if (r < 27 || r > 31 || room.cus < 8) return none;
   for (uint32_t i = 1; i < r; ++i)
     if (rot[i] != rot[0] + int(i)) return none;
   RotPlan best = none;
-  // us, pairs / shorter tiles: 9 queries of 30 rotations x 632 entries Galois 264 /
-  // 103, 28 of 30 x 1,405 507 / 196
   uint64_t least = rot_rounds_cost(q_all, r, n_all, vecs, room);
-  const uint64_t in_short_tiles = rot_short_cost(q_all, r, n_all, vecs, room);
-  least = in_short_tiles < least ? in_short_tiles : least;
   const uint32_t over = q_all % kPairQueries;
   for (int less = 0; less < 2; ++less) {
     if (less && (over == 0 || over > kPairQueries / 2)) break;
     const uint32_t q = less ? q_all - over : q_all;
     if (q == 0) break;
     const uint64_t per = uint64_t(q + kPairQueries - 1) / kPairQueries * vecs, nt = (n_all + kRotCols - 1) / kRotCols;
-    const uint64_t full = full_cols(n_all, per, room);
     for (int part = 0; part < 2; ++part) {
-      const uint64_t cols = part ? full : nt;
-      if (cols == 0 || (part && cols == nt)) break;
+      const uint64_t cols = part ? full_cols(n_all, per, room) : nt;
+      if (cols == 0 || (part && cols >= nt)) break;
       const uint64_t n = cols * kRotCols < n_all ? cols * kRotCols : n_all;
-      const uint64_t cost = kLaunchCost + pair_tile_cost(q) * ((cols * per + room.cus - 1) / room.cus) +
-                            rot_rounds_cost(q, r, n_all - n, vecs, room) +
+      if (part && rot_splits(uint64_t(q) * r, n_all - n, vecs, room) < 2) break;
+      const uint64_t cost = pair_cost(q, cols, vecs, room) + rot_rounds_cost(q, r, n_all - n, vecs, room) +
                             rot_rounds_cost(q_all - q, r, n_all, vecs, room);
-      if (cost < least) {
+      if (clearly_less(cost, least)) {
         least = cost;
         best = RotPlan{q, n};
       }

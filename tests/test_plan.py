@@ -44,15 +44,34 @@ def test_rows_of_a_rotation_tile(plan):
 
 
 def test_the_plan_and_the_launch_split_by_one_rule(plan):
-    """One tile of 31 rows over 128 entries: 32 parts of the replicated loop, of which the
-    plan counts 16, 16 of the Galois one; 20 tiles in 12 parts either way."""
+    """One tile of 31 rows over 128 entries: 32 parts of the replicated loop, 16 of the Galois
+    one; 20 tiles in 12 parts either way.  Three launches' costs and a part's of a tile."""
     assert plan.L.rot_splits(31, 128, 1, SCRATCH, 256, 0) == 32
     assert plan.L.rot_splits(31, 128, 1, SCRATCH, 256, 1) == 16
     for galois in (0, 1):
-        assert plan.L.rot_cost(1, 31, 128, 1, SCRATCH, 256, galois) == 2 * 2 + 56 // 16 + 2
+        assert plan.L.rot_cost(1, 31, 128, 1, SCRATCH, 256, galois) == 15 + 140 // (16 if galois else 32)
         assert plan.L.rot_splits(31, 1280, 2, SCRATCH, 256, galois) == 12
-        assert plan.L.rot_cost(1, 31, 1280, 2, SCRATCH, 256, galois) == 2 * 2 + 56 // 12 + 2
-        assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 2 + 56        # not lent
+        assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 5 + 140         # not lent
+
+
+def test_columns_are_taken_apart_by_eights(plan):
+    """A column tile's workgroups run on one of 8 XCDs: a first call of whole rounds has as many
+    columns on each, or some XCDs go one round further (80 queries of 22 rotations, 7 row tiles x
+    25 columns: 18 columns are 252 of 256 CUs' work, and 42 of 32 on two XCDs)."""
+    for q, r, n, v, galois in ((80, 22, 3133, 2, 0), (72, 17, 6927, 1, 1), (46, 15, 9001, 2, 0), (20, 13, 70_016, 2, 1)):
+        m = plan.L.first_cols(q, r, n, v, SCRATCH, 256, galois)
+        assert m == n or m % 1024 == 0, (q, r, n)
+    rot = list(range(-15, 16))
+    for q, n, galois in ((48, 8879, True), (66, 5190, False), (80, 3133, False), (30, 10_836, False)):
+        got = plan.plan(q, rot, n, 2, galois)
+        assert got[1] == n or got[1] % 1024 == 0, (q, n)
+
+
+def test_a_last_round_that_saves_little_is_not_taken_apart(plan):
+    """8 tiles on each XCD's 32 CUs past the whole rounds take hardly longer than 8 alone."""
+    assert plan.L.first_cols(80, 22, 3133, 2, SCRATCH, 256, 0) == 3133
+    assert plan.plan(48, list(range(-15, 16)), 8879, 2, True) == (48, 8879)
+    assert plan.plan(46, list(range(-15, 12)), 8293, 2, False) == (46, 8293)
 
 
 def test_rounds_are_those_of_the_device(plan):
