@@ -43,7 +43,7 @@ CALL_SOURCES = {
     "paper_2405_04463_amd/csrc/dot.hip":
         "c291e6983b90fa3d0d4d2fbb6d22aec324b54b9d46b2a1a793346d3d04b0b645",
     "paper_2405_04463_amd/csrc/plan.h":
-        "cfa88acf46c039e2c019fab9dcb3cdf68e4932a62c4287fd53c405410bd6e82c",
+        "5a1bb12982b1c01b6252e67017458e73c2cab4daa89b3da27aab2f6fd1e10ad1",
     "paper_2405_04463_amd/csrc/launch.h":
         "75a2832985b8a536ccddcbdf5c8041df22fbb8ca423d9a55465ea0f1d39f96ee",
     "paper_2405_04463_amd/csrc/api.cpp":

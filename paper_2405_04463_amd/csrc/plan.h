@@ -69,10 +69,16 @@ struct DotRoom {
 constexpr uint32_t rot_segs(bool galois) { return galois ? 16 : 32; }
 
 // Workgroups that share one tile's segments in a rotation call, one per CU (its
-// LDS).  The launch rounds a workgroup's segments up.
+// LDS), and no more than run at once on the XCDs of their columns: two rounds of
+// half a loop are no faster than a whole one (31 rotations, code and mask, us: 48
+// queries x 1,280 entries in 2 parts 430, whole in 192-row tiles 330; 24 x 1,792 in 3
+// parts 292, in 2 214; 80 x 512 in 4 parts 301, in 3 213).  The launch rounds a
+// workgroup's segments up.
 inline uint32_t rot_splits(uint64_t rows, uint64_t n, uint32_t vecs, const DotRoom& room) {
-  const uint64_t tiles = rot_tiles(rows, 256) * ((n + 127) / 128) * vecs;
-  return dot_splits(tiles, 1, room.segs, rows * n * vecs, room.bytes, room.cus);
+  const uint64_t mt = rot_tiles(rows, 256), nt = (n + 127) / 128;
+  uint32_t s = dot_splits(mt * nt * vecs, 1, room.segs, rows * n * vecs, room.bytes, room.cus);
+  while (s > 1 && room.cus >= 8 && !one_round(mt, nt * s, vecs, room.cus)) --s;
+  return s;
 }
 
 // Row tiles of a launch that go first: all but a last one of up to 128 rows,

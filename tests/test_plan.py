@@ -54,6 +54,21 @@ def test_the_plan_and_the_launch_split_by_one_rule(plan):
         assert plan.L.rot_cost(1, 31, 128, 1, 0, 256, galois) == 5 + 140         # not lent
 
 
+def test_parts_of_a_loop_run_at_once(plan):
+    """A column's parts run on one of 8 XCDs, 32 CUs: 6 row tiles x 10 columns x 2 vectors in 2
+    parts are 20 columns, 3 on some XCDs, 36 workgroups there."""
+    def at_once(rows, nt, vecs, parts):
+        return -(-rows // 256) * vecs * -(-nt * parts // 8) <= 32
+
+    assert plan.L.rot_splits(48 * 31, 1280, 2, SCRATCH, 256, 0) == 1
+    assert plan.L.rot_splits(24 * 31, 1792, 2, SCRATCH, 256, 0) == 2
+    for rows in (31, 260, 744, 1488, 2480):
+        for nt in range(1, 129):
+            for vecs in (1, 2):
+                s = plan.L.rot_splits(rows, 128 * nt, vecs, SCRATCH, 256, 0)
+                assert s == 1 or at_once(rows, nt, vecs, s), (rows, nt, vecs, s)
+
+
 def test_columns_are_taken_apart_by_eights(plan):
     """A column tile's workgroups run on one of 8 XCDs: a first call of whole rounds has as many
     columns on each, or some XCDs go one round further (80 queries of 22 rotations, 7 row tiles x
